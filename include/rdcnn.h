@@ -196,8 +196,11 @@ int rdcnn_set_kernel(rdcnn_t h, int kind, int depth, int cols_per_lane, int seg_
 
 /*
  * rdcnn_pass_config -- the pass shape later rdcnn_step calls use, with the
- * automatic choices resolved: *kind 1 (one thread per cell) or 2 (streamed),
- * *depth steps per pass, *cols_per_lane, *seg_rows output rows per wavefront
+ * automatic choices resolved: *kind 1 (one thread per cell), 2 (streamed) or 4
+ * (resident tiles, the automatic choice up to about 2400^2 cells; not a kind
+ * rdcnn_set_kernel takes), *depth steps per pass (kind 4: of a long run; other
+ * runs are cut evenly), *cols_per_lane, *seg_rows output rows per wavefront
+ * (kind 4: per workgroup)
  * (the paper's block/grid choice, Sec. II.B, made explicit).  Host-only, no
  * device work.  Errors: RDCNN_EINVAL (NULL argument).
  */

@@ -356,6 +356,16 @@ int run_model_steps(rdcnn_sim *h, long long n)
 {
     if (h->kind == 1) return fail(RDCNN_EINVAL, "rdcnn_step: the one-thread-per-cell kernel "
                                                 "exists for FitzHugh-Nagumo only");
+    rd::TilePlan plan;
+    if (h->kind == 0 && h->model == rd::MODEL_GRAY_SCOTT && rd::tile_plan(h->R, h->C, n, &plan)) {
+        for (long long i = 0; i < plan.passes; ++i) {
+            const hipError_t e = rd::launch_tile_gs(h->buf[h->cur], h->buf[1 - h->cur], h->R, h->C,
+                                                    h->bc, h->mparams, plan.at(i), h->stream);
+            if (e != hipSuccess) return hip_fail(e, "rdcnn_step: model kernel launch");
+            h->cur = 1 - h->cur;
+        }
+        return RDCNN_OK;
+    }
     int cpl, depth, seg;
     model_shape(h, &cpl, &depth, &seg);
     if (h->bc == RDCNN_BC_ZEROFLUX && !rd::model_mirror_exact(h->model, h->mparams)) depth = 1;
@@ -437,6 +447,18 @@ int run_steps(rdcnn_sim *h, long long n, float *rec, bool rec_even = false, int 
     }
     long long q = 0;
     int kind = h->kind, cpl = h->cpl, depth = h->depth, seg = h->seg_rows;
+    if (kind == 0 && !rec) {
+        rd::TilePlan plan;
+        if (rd::tile_plan(h->R, h->C, n, &plan)) {
+            for (long long i = 0; i < plan.passes; ++i) {
+                const hipError_t e = rd::launch_tile(h->buf[h->cur], h->buf[1 - h->cur], h->R, h->C,
+                                                     h->bc, h->g, plan.at(i), h->stream);
+                if (e != hipSuccess) return hip_fail(e, "rdcnn_step: kernel launch");
+                h->cur = 1 - h->cur;
+            }
+            return RDCNN_OK;
+        }
+    }
     if (kind == 3) kind = rec ? 0 : 2;  // forced shape for plain steps only
     if (kind == 0) {
         kind = 2;
@@ -1011,17 +1033,28 @@ int rdcnn_step_checkpoints(rdcnn_t h, long long T, long long S, float *ckpt_dev)
     if (e != hipSuccess) return hip_fail(e, who);
     // Passes stop at every multiple of S; the pass that ends at jS < T writes
     // its output straight into checkpoint j and the next pass reads it there.
+    // With resident tiles each segment is cut into its own plan's passes.
     const float *in = h->buf[h->cur];
+    rd::TilePlan plan;
+    long long pass = 0, plan_len = 0;
+    bool tiles = h->kind == 0;
     for (long long q = 0; q < T;) {
-        const long long bound = (q / S + 1) * S;
+        const long long bound = (q / S + 1) * S < T ? (q / S + 1) * S : T;
         long long k = kind == 1 ? 1 : depth;
-        if (k > T - q) k = T - q;
+        if (q % S == 0 && tiles) {
+            pass = 0;
+            if (bound - q != plan_len) tiles = rd::tile_plan(h->R, h->C, bound - q, &plan);
+            plan_len = bound - q;
+        }
+        if (tiles) k = plan.at(pass).K;
         if (k > bound - q) k = bound - q;
         const long long end = q + k;
         float *out = end % S == 0 && end < T ? ckpt_dev + (size_t)(end / S) * state
                      : in == h->buf[0]      ? h->buf[1]
                                             : h->buf[0];
-        if (kind == 1) {
+        if (tiles) {
+            e = rd::launch_tile(in, out, h->R, h->C, h->bc, h->g, plan.at(pass++), h->stream);
+        } else if (kind == 1) {
             e = rd::launch_naive(in, out, h->R, h->C, h->bc, h->g, h->stream);
         } else {
             rd::StreamGeom geom;
@@ -1271,6 +1304,14 @@ int rdcnn_pass_config(rdcnn_t h, int *kind, int *depth, int *cols_per_lane, int 
     if (!h || !kind || !depth || !cols_per_lane || !seg_rows)
         return fail(RDCNN_EINVAL, "rdcnn_pass_config: NULL argument");
     int k = h->kind == 3 ? 2 : h->kind, cpl = h->cpl, d = h->depth, seg = h->seg_rows;
+    rd::TilePlan plan;
+    if (h->kind == 0 && h->model != rd::MODEL_CNN && rd::tile_plan(h->R, h->C, 1 << 20, &plan)) {
+        *kind = 4;
+        *depth = plan.base.K;
+        *cols_per_lane = plan.base.cpl;
+        *seg_rows = rd::tile_out_rows(plan.base);
+        return RDCNN_OK;
+    }
     if (h->model != rd::MODEL_FHN) {
         if (k == 0) k = 2;
         model_shape(h, &cpl, &d, &seg);

@@ -76,6 +76,32 @@ hipError_t launch_stream(const float *in, float *out, int R, int C, int bc, cons
                          long long rec_q0 = 0, bool rec_even = false, bool skip_level0 = false,
                          int rec_every = 1);
 
+// Resident-tile passes (rd_tile_body.h): `w` wavefronts per workgroup, each two
+// blocks of rw rows x 32*cpl columns, K steps; a tile writes 2*w*rw - 2*K rows.
+struct TileShape {
+    int cpl, rw, w, K;
+};
+constexpr int kMaxTileDepth = 16;
+// Largest grid that takes them.  us per step, resident tiles against the best
+// streamed shape: 2048^2 3.3 / 4.3, 2304^2 4.51 / 5.11, 2400^2 5.22 / 5.62.
+constexpr long long kMaxTileCells = 6000000;
+inline int tile_out_rows(const TileShape &s) { return 2 * s.w * s.rw - 2 * s.K; }
+
+// T steps as `passes` passes: the first `deeper` of shape `deep`, the others of
+// shape `base` (one step shallower).
+struct TilePlan {
+    long long passes = 0, deeper = 0;
+    TileShape base{}, deep{};
+    const TileShape &at(long long i) const { return i < deeper ? deep : base; }
+};
+// The fastest plan by the launcher's cost model; false if the grid is for the
+// streamed kernel.
+bool tile_plan(int R, int C, long long T, TilePlan *plan);
+hipError_t launch_tile(const float *in, float *out, int R, int C, int bc, const Gene &g,
+                       const TileShape &shape, hipStream_t s);
+hipError_t launch_tile_gs(const float *in, float *out, int R, int C, int bc, const float *params,
+                          const TileShape &shape, hipStream_t s);
+
 // Cell models other than FitzHugh-Nagumo on the same streamed kernel
 // (rd_models.h).  Their passes take depth 1, 2, 4 or 8 and cols_per_lane 1, 2
 // or, for models instantiated that wide (model_max_cpl), 4.

@@ -1,0 +1,10 @@
+// rd_tile.h -- tables of the resident-tile kernel instances (rd_tile_*.hip).
+#pragma once
+
+#include "rd_launch.h"
+#include "rd_tile_body.h"
+
+namespace rd {
+TileFn<ModelFHN> tile_fn_fhn(int cpl, int rw);
+TileFn<ModelGrayScott> tile_fn_gs(int cpl, int rw);
+}  // namespace rd

@@ -1,0 +1,330 @@
+// rd_tile_body.h -- resident-tile passes: K steps of a cell model on tiles held
+// whole in one workgroup's registers.
+//
+// A workgroup of W wavefronts owns a tile of 32*CPL columns by 2*W*RW rows,
+// halo included.  A wavefront holds two blocks of RW rows, one per 32-lane
+// half, CPL adjacent columns per lane; block b is rows [b RW, (b+1) RW) of the
+// tile.  All K steps run on the registers; between steps each block publishes
+// its first and last row in LDS (two buffers in turn, one barrier per step) for
+// the blocks above and below.  After s steps the outermost s rows and columns
+// of the tile hold garbage, so the inner R x C part shrinks by K on each side;
+// only that part is written.  The halo is read from the boundary-extended grid
+// (map_index), as in the streamed kernel, so results are bit-identical to it.
+//
+// Why this shape.  A streamed pass on a grid of up to ~2300^2 cells is bound by
+// latency: few wavefronts, each walking its rows one after another through K
+// dependent levels.  Here the rows of a step are independent.  Neighbour
+// columns come from ds_swizzle (rotate within 32 lanes), not from DPP: on gfx950
+// two wavefronts of a SIMD issue plain float32 VALU instructions side by side
+// (one per 2.3-2.9 cycles measured, against 4.1-4.3 in code that holds a DPP
+// shift even once in 32 instructions), and a swizzle costs about 7.  LDS writes
+// are the slow side of LDS here (78 bytes per clock against 200-250 read), which
+// is why only the two outer rows of a block are written.  Measured per step,
+// against the streamed kernel at its tuned shape: 128^2 0.54 us (1.17), 256^2
+// 0.55 (1.23), 512^2 0.75 (1.57), 1024^2 1.39 (2.26), 2048^2 3.6 (4.3).
+#pragma once
+
+#include <type_traits>
+
+#include "rd_models.h"
+#include "rd_stream.h"
+
+namespace rd {
+
+template <class M>
+struct TileStepArgsT {
+    TileArgs t;  // h = output rows of a tile, wout / kpad as for a strip of 32*CPL columns
+    const float *in;
+    float *out;
+    typename M::Params g;
+    int K;  // steps of the pass
+};
+
+// Barrier that orders LDS accesses only (global stores stay in flight).
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Lane i of each 32-lane half receives lane i-1's (i+1's) value of its half,
+// rotating (ds_swizzle rotate mode: bit 10 the direction, bits 9:5 the count).
+__device__ __forceinline__ float half_from_left(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, x), 0xC420));
+}
+__device__ __forceinline__ float half_from_right(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, x), 0xC020));
+}
+
+// One lane's columns of one row, and the columns beside them.
+template <int CPL>
+struct Row {
+    float u[CPL], v[CPL];
+};
+struct Edge {
+    float lu, ru, lv, rv;
+};
+
+template <int CPL>
+__device__ __forceinline__ Edge edge_of(const Row<CPL> &r)
+{
+    return Edge{half_from_left(r.u[CPL - 1]), half_from_right(r.u[0]),
+                half_from_left(r.v[CPL - 1]), half_from_right(r.v[0])};
+}
+
+// D = the model's update of row C between rows N and S (D may alias any of them).
+template <class M, int CPL>
+__device__ __forceinline__ void row_update(const typename M::Params &g, const Row<CPL> &N,
+                                           const Row<CPL> &C, const Row<CPL> &S, const Edge &E,
+                                           Row<CPL> &D)
+{
+    Row<CPL> o;
+#pragma unroll
+    for (int e = 0; e < CPL; ++e) {
+        Nbhd n;
+        n.u = n.y = C.u[e];
+        n.v = C.v[e];
+        n.uN = N.u[e];
+        n.uS = S.u[e];
+        n.vN = N.v[e];
+        n.vS = S.v[e];
+        n.uW = e == 0 ? E.lu : C.u[e - 1];
+        n.uE = e == CPL - 1 ? E.ru : C.u[e + 1];
+        n.vW = e == 0 ? E.lv : C.v[e - 1];
+        n.vE = e == CPL - 1 ? E.rv : C.v[e + 1];
+        M::update(g, n, o.u[e], o.v[e]);
+    }
+    D = o;
+}
+
+// Column addressing of one lane.  FAST tiles move a lane's columns with one
+// vector access: inside the grid always (rows need only 4-byte alignment), and
+// at its edges where C % CPL == 0, since a lane's columns then map to one
+// aligned run of columns, reversed (`rev`) where the zero-flux mirror folds them.
+// Other tiles map and move each column on its own.
+template <int CPL>
+struct HalfTile {
+    int cx;                // first column of the lane (boundary-extended)
+    bool lane_out;         // the lane's columns are output columns
+    bool rev, any_rev;     // this lane's columns are mirrored; some lane's are
+    unsigned vo, mo[CPL];  // byte offsets: of the run, of each mapped column
+
+    __device__ __forceinline__ void setup(const TileArgs &A, int x0)
+    {
+        const int oc = CPL * ((int)threadIdx.x & 31);
+        cx = x0 + oc;
+        const int m0 = map_index(cx, A.C, A.bc), m1 = map_index(cx + CPL - 1, A.C, A.bc);
+        rev = m1 < m0;
+        any_rev = A.bc != BC_PERIODIC && (x0 < 0 || x0 + 32 * CPL > A.C);
+        vo = 4u * (unsigned)min(m0, m1);
+#pragma unroll
+        for (int e = 0; e < CPL; ++e) mo[e] = 4u * (unsigned)map_index(cx + e, A.C, A.bc);
+        lane_out = oc >= A.kpad && oc < A.kpad + A.wout && cx < A.C;
+    }
+
+    template <bool FAST>
+    __device__ __forceinline__ void load(const Buf &b, unsigned ro, float (&x)[CPL]) const
+    {
+        if (FAST) {
+            buf_load<CPL>(b, vo + ro, 0, x);
+        } else {
+#pragma unroll
+            for (int e = 0; e < CPL; ++e) x[e] = buf_load1(b, mo[e] + ro, 0);
+        }
+    }
+
+    // output columns lie inside the grid, where vo is the lane's own column
+    template <bool FAST>
+    __device__ __forceinline__ void store(const Buf &b, unsigned ro, int C, const float (&x)[CPL]) const
+    {
+        if (FAST) {
+            buf_store<CPL>(b, vo + ro, 0, x);
+        } else {
+#pragma unroll
+            for (int e = 0; e < CPL; ++e)
+                if (cx + e < C) buf_store1(b, 4u * (unsigned)(cx + e) + ro, 0, x[e]);
+        }
+    }
+
+    __device__ __forceinline__ void unmirror(float (&x)[CPL]) const
+    {
+#pragma unroll
+        for (int e = 0; e < CPL / 2; ++e) {
+            const float a = x[e], b = x[CPL - 1 - e];
+            x[e] = rev ? b : a;
+            x[CPL - 1 - e] = rev ? a : b;
+        }
+    }
+};
+
+// LDS bytes of a workgroup: [buffer][layer][block][first, last row][32 lanes].
+constexpr int tile_lds_bytes(int cpl, int w) { return 2 * 2 * (2 * w) * 2 * 32 * 4 * cpl; }
+
+template <class M, int CPL, int RW, bool FAST>
+__device__ __forceinline__ void tile_body(const TileStepArgsT<M> &A, int x0, int y0, int y1, char *smem)
+{
+    const int C = A.t.C, R = A.t.R, bc = A.t.bc, K = A.K;
+    const unsigned pbytes = 4u * (unsigned)R * (unsigned)C;
+    const Buf iu(A.in, pbytes), iv(A.in + (size_t)R * C, pbytes);
+    const Buf ou(A.out, pbytes), ov(A.out + (size_t)R * C, pbytes);
+    const typename M::Params g = A.g;
+    const int W = (int)blockDim.y;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
+    const int lane = (int)threadIdx.x, half = lane >> 5;
+    HalfTile<CPL> t;
+    t.setup(A.t, x0);
+    const int q0 = 2 * w * RW;                     // first tile row of the wavefront
+    const int ra = y0 - K + q0, rb = ra + RW;      // first grid row of its two blocks
+    const int H = y1 - y0 + 2 * K;                 // tile rows in use
+    const int rlast = y1 + K - 1;                  // last one; rows past it repeat it
+    // Rows live in slots 1..RW before an even step and 0..RW-1 before an odd
+    // one: a step writes each new row over the slot of the row just used up, so
+    // the rows shift by one slot down and back up without register copies.
+    Row<CPL> x[RW + 1];
+#pragma unroll
+    for (int i = 0; i < RW; ++i) {
+        const unsigned r0 = row_off(min(ra + i, rlast), R, C, bc);
+        const unsigned r1 = row_off(min(rb + i, rlast), R, C, bc);
+        const unsigned ro = half ? r1 : r0;
+        t.template load<FAST>(iu, ro, x[i + 1].u);
+        t.template load<FAST>(iv, ro, x[i + 1].v);
+    }
+    if (FAST && t.any_rev) {
+#pragma unroll
+        for (int i = 1; i <= RW; ++i) {
+            t.unmirror(x[i].u);
+            t.unmirror(x[i].v);
+        }
+    }
+    using V = vecf<CPL>;
+    const int b = 2 * w + half;
+    const int plane = 2 * W * 64;
+    V *sm = (V *)smem + (lane & 31);
+    V *own = sm + b * 64;
+    const V *above = sm + max(b - 1, 0) * 64 + 32;         // last row of the block above
+    const V *below = sm + min(b + 1, 2 * W - 1) * 64;      // first row of the block below
+    auto put = [&](int buf, int side, const Row<CPL> &r) __attribute__((always_inline)) {
+        V a, c;
+#pragma unroll
+        for (int e = 0; e < CPL; ++e) {
+            a[e] = r.u[e];
+            c[e] = r.v[e];
+        }
+        own[buf * 2 * plane + side * 32] = a;
+        own[buf * 2 * plane + plane + side * 32] = c;
+    };
+    auto get = [&](int buf, const V *p) __attribute__((always_inline)) {
+        Row<CPL> r;
+        const V a = p[buf * 2 * plane], c = p[buf * 2 * plane + plane];
+#pragma unroll
+        for (int e = 0; e < CPL; ++e) {
+            r.u[e] = a[e];
+            r.v[e] = c[e];
+        }
+        return r;
+    };
+    // Edge columns of each row, fetched as soon as the row is made.
+    Edge E[RW];
+    put(0, 0, x[1]);
+    put(0, 1, x[RW]);
+#pragma unroll
+    for (int i = 0; i < RW; ++i) E[i] = edge_of(x[i + 1]);
+    lds_barrier();
+    // Step s makes valid rows s+1 .. H-s-2; a wavefront with none of them rests.
+    auto active = [&](int s) { return q0 + 2 * RW > s + 1 && q0 < H - s - 1; };
+    auto even_step = [&](int s) __attribute__((always_inline)) {
+        if (active(s)) {
+            const Row<CPL> nN = get(0, above), nS = get(0, below);
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                row_update<M, CPL>(g, i == 0 ? nN : x[i], x[i + 1],
+                                   i == RW - 1 ? nS : x[i + 2 > RW ? RW : i + 2], E[i], x[i]);
+                if (i == 0) put(1, 0, x[0]);
+                if (i == RW - 1) put(1, 1, x[RW - 1]);
+                E[i] = edge_of(x[i]);
+            }
+        }
+        lds_barrier();
+    };
+    auto odd_step = [&](int s) __attribute__((always_inline)) {
+        if (active(s)) {
+            const Row<CPL> nS = get(1, below), nN = get(1, above);
+#pragma unroll
+            for (int i = RW - 1; i >= 0; --i) {
+                row_update<M, CPL>(g, i == 0 ? nN : x[i < 1 ? 0 : i - 1], x[i],
+                                   i == RW - 1 ? nS : x[i + 1], E[i], x[i + 1]);
+                if (i == RW - 1) put(0, 1, x[RW]);
+                if (i == 0) put(0, 0, x[1]);
+                E[i] = edge_of(x[i + 1]);
+            }
+        }
+        lds_barrier();
+    };
+    auto store = [&](auto slot0) __attribute__((always_inline)) {
+        if (!t.lane_out) return;
+        const int r0 = half ? rb : ra;
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            const int r = r0 + i;
+            if (r >= y0 && r < y1) {
+                const unsigned ro = 4u * (unsigned)r * (unsigned)C;
+                t.template store<FAST>(ou, ro, C, x[i + decltype(slot0)::value].u);
+                t.template store<FAST>(ov, ro, C, x[i + decltype(slot0)::value].v);
+            }
+        }
+    };
+    for (int s = 0; s + 2 <= K; s += 2) {
+        even_step(s);
+        odd_step(s + 1);
+    }
+    if (K & 1) {
+        even_step(K - 1);
+        store(std::integral_constant<int, 0>{});
+    } else {
+        store(std::integral_constant<int, 1>{});
+    }
+}
+
+template <class M, int CPL, int RW>
+__global__ __launch_bounds__(1024) void tile_step_kernel(TileStepArgsT<M> A)
+{
+    extern __shared__ __align__(16) char tile_smem[];
+    const int tl = xcd_tile(blockIdx.x, A.t.per_xcd);
+    if (tl >= A.t.ntiles) return;
+    const int strip = tl / A.t.nsegs, seg = tl - strip * A.t.nsegs;
+    const int x0 = strip * A.t.wout - A.t.kpad, y0 = seg * A.t.h, y1 = min(y0 + A.t.h, A.t.R);
+    if (A.t.vec_ok || (x0 >= 0 && x0 + 32 * CPL <= A.t.C))
+        tile_body<M, CPL, RW, true>(A, x0, y0, y1, tile_smem);
+    else
+        tile_body<M, CPL, RW, false>(A, x0, y0, y1, tile_smem);
+}
+
+template <class M>
+using TileFn = void (*)(TileStepArgsT<M>);
+
+template <class M, int CPL>
+TileFn<M> pick_tile_rows(int rw)
+{
+    if constexpr (CPL == 2) {  // one-row blocks only pay on the smallest grids
+        if (rw == 1) return &tile_step_kernel<M, CPL, 1>;
+    }
+    switch (rw) {
+        case 2: return &tile_step_kernel<M, CPL, 2>;
+        case 3: return &tile_step_kernel<M, CPL, 3>;
+        case 4: return &tile_step_kernel<M, CPL, 4>;
+        case 5: return &tile_step_kernel<M, CPL, 5>;
+        case 6: return &tile_step_kernel<M, CPL, 6>;
+        default: return nullptr;
+    }
+}
+
+template <class M>
+TileFn<M> pick_tile(int cpl, int rw)
+{
+    return cpl == 2 ? pick_tile_rows<M, 2>(rw) : cpl == 4 ? pick_tile_rows<M, 4>(rw) : nullptr;
+}
+
+}  // namespace rd

@@ -1,0 +1,6 @@
+// Resident-tile kernel instances: FitzHugh-Nagumo (rd_tile_body.h).
+#include "rd_tile.h"
+
+namespace rd {
+TileFn<ModelFHN> tile_fn_fhn(int cpl, int rw) { return pick_tile<ModelFHN>(cpl, rw); }
+}  // namespace rd

@@ -10,7 +10,9 @@ candidate settings
     cols_per_lane  1, 2 or 4 adjacent columns per lane (strip = 64 * cols)
     seg_rows       output rows per wavefront (0 = the library's choice)
 
-with HIP events on the current stream and keeps the fastest.  For a batch it
+with HIP events on the current stream and keeps the fastest.  For "forward" the
+library's automatic choice (which also knows the resident-tile passes, not only
+streamed shapes) competes as the setting (0, 0, 0).  For a batch it
 then times, one size class at a time (largest total cells first), the rows
 per tile of that class with the others fixed (rdcnn_batch_set_class_seg_rows):
 steps per pass and columns per lane are per launch, and one launch covers
@@ -159,12 +161,13 @@ def tune(mode: str, rows: int, cols: int, bc: str = "zeroflux", gene=None, budge
         adj = torch.randn((2, rows, cols), device="cuda")
         tmp = torch.empty_like(adj)
         dth = torch.zeros(8, dtype=torch.float64, device="cuda")
-    for cand in candidates(mode, rows, cols):
+    auto = [(0, 0, 0)] if mode == "forward" else []
+    for cand in auto + candidates(mode, rows, cols):
         if time.time() > t_end:
             break
         depth, cpl, seg = cand
         if mode == "forward":
-            sim.set_kernel(2, depth, cpl, seg)
+            sim.set_kernel(2 if depth else 0, depth, cpl, seg)
             t = run(lambda: sim.step(T))
             rate = rows * cols * T / t / 1e9
         elif mode in ("record", "record_even"):
@@ -274,7 +277,7 @@ def apply(obj, path: str = None, grad: bool = False, modes=None):
         if not cfg:
             continue
         if mode == "forward":  # plain steps only: recording keeps its own shapes
-            obj.set_kernel(3, *cfg)
+            obj.set_kernel(3 if cfg[0] else 0, *cfg)
         elif mode == "record_even":
             obj.set_kernel(2, *cfg)
         else:
