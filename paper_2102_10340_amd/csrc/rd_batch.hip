@@ -182,9 +182,11 @@ struct rdcnn_batch {
     int n, bc;
     int use_lds;                // hold small instances in LDS for a whole run
     int lds_limit;              // frame cells one workgroup's LDS can hold
-    std::vector<char> in_lds;   // instance i runs in the in-LDS kernel
-    int *lds_ids_dev;           // their indices
+    std::vector<char> in_lds;   // instance i runs whole in one workgroup
+    int *lds_ids_dev;           // those of the in-LDS kernel
     int lds_count, lds_frame;   // how many, largest frame
+    rd::WholeInst *whole_dev;   // those held in registers: two columns per lane first, then four
+    int whole_count[2], whole_waves[2];
     std::vector<int> R, C;
     std::vector<int> seg_of;    // per-instance rows per tile of plain passes (0: the batch's)
     std::vector<long long> off;
@@ -292,15 +294,20 @@ void free_lds(rdcnn_batch *b)
     if (b->lds_ids_dev) (void)hipFree(b->lds_ids_dev);
     b->lds_ids_dev = nullptr;
     b->lds_count = b->lds_frame = 0;
+    if (b->whole_dev) (void)hipFree(b->whole_dev);
+    b->whole_dev = nullptr;
+    for (int q = 0; q < 2; ++q) b->whole_count[q] = b->whole_waves[q] = 0;
     b->in_lds.assign(b->n, 0);
 }
 
-// Decide which instances the in-LDS kernel takes and upload their indices.
+// Decide which instances run whole in one workgroup (in its registers where
+// their shape cuts evenly, else in its LDS) and upload their lists.
 int setup_lds(rdcnn_batch *b)
 {
     free_lds(b);
     if (!b->use_lds) return RDCNN_OK;
     std::vector<int> ids;
+    std::vector<rd::WholeInst> whole[2];
     int frame = 0;
     for (int i = 0; i < b->n; ++i) {
         const int R = b->R[i], C = b->C[i];
@@ -310,8 +317,28 @@ int setup_lds(rdcnn_batch *b)
         const long long fr = (long long)(runs * m + 2) * (C + 2);  // frame incl. unstored rows
         if (m <= rd::kLdsRun && fr <= b->lds_limit) {
             b->in_lds[i] = 1;
+            int cpl, rw;
+            if (rd::whole_shape(R, C, &cpl, &rw)) {
+                const int waves = (R / rw + 1) / 2, q = cpl == 4;
+                if (rd::whole_lds_bytes(cpl, waves) <= b->lds_limit * (int)sizeof(float2)) {
+                    whole[q].push_back(rd::WholeInst{i, rw});
+                    if (waves > b->whole_waves[q]) b->whole_waves[q] = waves;
+                    continue;
+                }
+            }
             ids.push_back(i);
             if (fr > frame) frame = (int)fr;
+        }
+    }
+    for (int q = 0; q < 2; ++q) b->whole_count[q] = (int)whole[q].size();
+    if (b->whole_count[0] + b->whole_count[1] > 0) {
+        whole[0].insert(whole[0].end(), whole[1].begin(), whole[1].end());
+        const size_t bytes = sizeof(rd::WholeInst) * whole[0].size();
+        hipError_t e = hipMalloc((void **)&b->whole_dev, bytes);
+        if (e == hipSuccess) e = hipMemcpy(b->whole_dev, whole[0].data(), bytes, hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            free_lds(b);
+            return bfail(RDCNN_ENOMEM, "batch: whole-instance table: %s", hipGetErrorString(e));
         }
     }
     if (ids.empty()) return RDCNN_OK;
@@ -493,18 +520,32 @@ int state_depth_cap(const rdcnn_batch *b, int want)
     return k;
 }
 
+// All T steps of the instances that run whole in one workgroup, into buf[after].
+int launch_whole(rdcnn_batch *b, long long T, int after)
+{
+    hipError_t e = hipSuccess;
+    for (int q = 0; q < 2 && e == hipSuccess; ++q)
+        if (b->whole_count[q] > 0)
+            e = rd::launch_batch_whole(b->insts_dev, b->whole_dev + (q ? b->whole_count[0] : 0),
+                                       b->whole_count[q], q ? 4 : 2, b->whole_waves[q],
+                                       b->buf[b->cur], b->buf[after], b->bc, T, b->stream);
+    if (e == hipSuccess && b->lds_count > 0)
+        e = rd::launch_batch_lds(b->insts_dev, b->lds_ids_dev, b->lds_count, b->lds_frame,
+                                 b->buf[b->cur], b->buf[after], b->bc, T, b->stream);
+    if (e != hipSuccess) return bfail(RDCNN_EHIP, "batch: in-LDS launch: %s", hipGetErrorString(e));
+    return RDCNN_OK;
+}
+
 // Enqueue the launches of T steps; cur flips once per streamed launch.  The
 // in-LDS instances go first, in one launch, and write their final state to the
 // buffer that will be current after the T steps.
 int enqueue_steps(rdcnn_batch *b, long long T, int cpl, int depth)
 {
-    if (b->lds_count > 0 && T > 0) {
+    if (T > 0) {
         const long long passes = (T + depth - 1) / depth;
         const int after = (passes % 2) ? 1 - b->cur : b->cur;
-        hipError_t e = rd::launch_batch_lds(b->insts_dev, b->lds_ids_dev, b->lds_count,
-                                            b->lds_frame, b->buf[b->cur], b->buf[after], b->bc,
-                                            T, b->stream);
-        if (e != hipSuccess) return bfail(RDCNN_EHIP, "batch: in-LDS launch: %s", hipGetErrorString(e));
+        const int rc = launch_whole(b, T, after);
+        if (rc != RDCNN_OK) return rc;
     }
     while (T > 0) {
         const int k = (int)(T < depth ? T : depth);
@@ -619,6 +660,8 @@ int rdcnn_batch_create(rdcnn_batch_t *out, int n, const int *rows, const int *co
     b->use_lds = 1;
     b->lds_ids_dev = nullptr;
     b->lds_count = b->lds_frame = 0;
+    b->whole_dev = nullptr;
+    for (int q = 0; q < 2; ++q) b->whole_count[q] = b->whole_waves[q] = 0;
     b->in_lds.assign(n, 0);
     {
         int dev = 0, lds = 0;
@@ -906,7 +949,7 @@ int rdcnn_batch_stats(rdcnn_batch_t b, const float *prev, const float *ref, floa
 int rdcnn_batch_lds_instances(rdcnn_batch_t b, int *count)
 {
     if (!b || !count) return bfail(RDCNN_EINVAL, "rdcnn_batch_lds_instances: NULL argument");
-    *count = b->lds_count;
+    *count = b->lds_count + b->whole_count[0] + b->whole_count[1];
     return RDCNN_OK;
 }
 

@@ -202,6 +202,17 @@ hipError_t launch_batch_adjoint_finish(const double *partial, const int *first, 
 hipError_t launch_batch_lds(const BatchInst *insts, const int *ids, int count, int frame_cells,
                             const float *in, float *out, int bc, long long T, hipStream_t s);
 
+// All T steps of `count` small instances held whole in one workgroup's registers
+// (rd_batch_whole.hip), `waves` wavefronts each.
+struct WholeInst {
+    int inst, rw;  // instance, rows per block
+};
+bool whole_shape(int R, int C, int *cpl, int *rw);
+int whole_lds_bytes(int cpl, int waves);
+hipError_t launch_batch_whole(const BatchInst *insts, const WholeInst *list, int count, int cpl,
+                              int waves, const float *in, float *out, int bc, long long T,
+                              hipStream_t s);
+
 // Per-instance atlas statistics: chunks of at most kStatChunk cells, one
 // workgroup each, folded per instance in chunk order (first[i] .. first[i+1]).
 constexpr int kStats = 8;
