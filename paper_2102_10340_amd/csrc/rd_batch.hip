@@ -626,6 +626,7 @@ int rdcnn_batch_create(rdcnn_batch_t *out, int n, const int *rows, const int *co
         rd::Gene g{p.dt, p.a, p.b, p.eps, p.c, p.k3, p.Du, p.Dv};
         b->g[i] = g;
         inst[i].off = offsets[i];
+        inst[i].xoff = x_offsets[i];
         inst[i].R = rows[i];
         inst[i].C = cols[i];
         inst[i].g = g;
@@ -677,9 +678,10 @@ int rdcnn_batch_create(rdcnn_batch_t *out, int n, const int *rows, const int *co
         return bfail(RDCNN_ENOMEM, "rdcnn_batch_create: instance table: %s", hipGetErrorString(e));
     }
     e = hipMemcpy(b->insts_dev, inst.data(), sizeof(rd::BatchInst) * n, hipMemcpyHostToDevice);
-    for (int i = 0; i < n && e == hipSuccess; ++i)
-        e = rd::launch_init(x_dev + x_offsets[i], ka, buf0_dev + offsets[i],
-                            (long long)rows[i] * cols[i], b->stream);
+    long long most = 0;
+    for (int i = 0; i < n; ++i) most = std::max(most, (long long)rows[i] * cols[i]);
+    if (e == hipSuccess)
+        e = rd::launch_batch_init(b->insts_dev, n, most, x_dev, ka, buf0_dev, b->stream);
     if (e != hipSuccess) {
         (void)hipFree(b->insts_dev);
         delete b;

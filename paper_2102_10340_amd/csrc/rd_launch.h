@@ -161,7 +161,8 @@ hipError_t launch_adjoint_finish(const double *partial, int ntiles, const Gene &
 
 // One instance of a batch: its offset in the packed buffers, size and gene.
 struct BatchInst {
-    long long off;  // float offset of the instance in a packed buffer
+    long long off;   // float offset of the instance in a packed buffer
+    long long xoff;  // float offset of its initial image
     int R, C;
     Gene g;
 };
@@ -212,6 +213,11 @@ int whole_lds_bytes(int cpl, int waves);
 hipError_t launch_batch_whole(const BatchInst *insts, const WholeInst *list, int count, int cpl,
                               int waves, const float *in, float *out, int bc, long long T,
                               hipStream_t s);
+
+// u = v = ka * x for every instance of a batch, in one launch; max_cells: cells of
+// the largest instance.
+hipError_t launch_batch_init(const BatchInst *insts, int n, long long max_cells, const float *x,
+                             float ka, float *state, hipStream_t s);
 
 // Per-instance atlas statistics: chunks of at most kStatChunk cells, one
 // workgroup each, folded per instance in chunk order (first[i] .. first[i+1]).
