@@ -64,7 +64,8 @@ def scan(du, dv, gene, x, T: int, dT: int, bc: str = "periodic", theta_far: floa
     stats at T [len(du), len(dv), 8] as numpy)."""
     genes = [dict(gene, Du=float(a), Dv=float(b)) for a in du for b in dv]
     b = Batch([x] * len(genes), genes, bc)
-    ref = torch.tensor([rest_state(g)[0] for g in genes], dtype=torch.float32, device=x.device)
+    # the rest state does not depend on Du and Dv, the only values that vary
+    ref = torch.full((len(genes),), rest_state(genes[0])[0], dtype=torch.float32, device=x.device)
     b.step(T - dT)
     prev = b.snapshot()
     s_prev = b.stats(None, ref, theta_far, theta_move)
