@@ -391,21 +391,32 @@ int run_model_steps(rdcnn_sim *h, long long n)
 // every / 2 states, i.e. rec + i * every states), and the next pass reads its
 // input from there and records from level 2 on, so each recorded state is
 // written once.  No pass reads a slot it writes.  The last pass writes
-// last_out.  The first pass records its input as s_0.
+// last_out.  The first pass records its input as s_0.  With tile_depth > 0 the
+// passes run on resident tiles, tile_depth (even) steps each; cpl, depth and seg
+// are the streamed passes'.
 int record_even_chain(const rdcnn_sim *h, const float *in, long long n, float *rec, int every,
-                      float *last_out, int cpl, int depth, int seg, hipStream_t s, const char *who)
+                      float *last_out, int tile_depth, int cpl, int depth, int seg, hipStream_t s,
+                      const char *who)
 {
     const size_t state = 2 * (size_t)h->R * h->C;
+    if (tile_depth > 0) depth = tile_depth;
     long long q = 0;
     while (n > 0) {
         const int k = (int)(n < depth ? n : depth);
         float *out = n == k ? last_out : rec + (size_t)((q + k) / 2) * every * state;
-        rd::StreamGeom geom;
-        if (!rd::stream_geometry(h->R, h->C, cpl, k, seg, &geom))
-            return fail(RDCNN_EINVAL, "%s: cannot tile %dx%d with cpl=%d depth=%d", who, h->R, h->C,
-                        cpl, k);
-        hipError_t e = rd::launch_stream(in, out, h->R, h->C, h->bc, h->g, geom, s, rec, q / 2, true,
-                                         q > 0, every);
+        hipError_t e;
+        if (tile_depth > 0) {
+            const rd::TileRecord tr{rec + (size_t)(q / 2) * every * state, every, q == 0};
+            e = rd::launch_tile(in, out, h->R, h->C, h->bc, h->g, rd::tile_shape(h->R, h->C, k), s,
+                                &tr);
+        } else {
+            rd::StreamGeom geom;
+            if (!rd::stream_geometry(h->R, h->C, cpl, k, seg, &geom))
+                return fail(RDCNN_EINVAL, "%s: cannot tile %dx%d with cpl=%d depth=%d", who, h->R,
+                            h->C, cpl, k);
+            e = rd::launch_stream(in, out, h->R, h->C, h->bc, h->g, geom, s, rec, q / 2, true, q > 0,
+                                  every);
+        }
         if (e != hipSuccess) return hip_fail(e, who);
         in = out;
         n -= k;
@@ -460,6 +471,15 @@ int run_steps(rdcnn_sim *h, long long n, float *rec, bool rec_even = false, int 
         }
     }
     if (kind == 3) kind = rec ? 0 : 2;  // forced shape for plain steps only
+    if (kind == 0 && rec && rec_even && n > 0) {
+        const int td = rd::tile_record_depth(h->R, h->C, n);
+        if (td > 0) {
+            const int rc = record_even_chain(h, h->buf[h->cur], n, rec, every, h->buf[1 - h->cur], td,
+                                             0, 0, 0, h->stream, "rdcnn_step");
+            if (rc == RDCNN_OK) h->cur = 1 - h->cur;
+            return rc;
+        }
+    }
     if (kind == 0) {
         kind = 2;
         auto_config(h, &cpl, &depth, &seg, rec != nullptr, rec_even);
@@ -484,8 +504,8 @@ int run_steps(rdcnn_sim *h, long long n, float *rec, bool rec_even = false, int 
         }
     }
     if (rec && rec_even && kind == 2 && depth >= 2 && n > 0) {
-        const int rc = record_even_chain(h, h->buf[h->cur], n, rec, every, h->buf[1 - h->cur], cpl,
-                                         depth, seg, h->stream, "rdcnn_step");
+        const int rc = record_even_chain(h, h->buf[h->cur], n, rec, every, h->buf[1 - h->cur], 0,
+                                         cpl, depth, seg, h->stream, "rdcnn_step");
         if (rc != RDCNN_OK) return rc;
         h->cur = 1 - h->cur;
         return RDCNN_OK;
@@ -852,11 +872,12 @@ int rdcnn_adjoint(rdcnn_t h, const float *states_dev, long long S, float *adj_de
 
 namespace {
 
-// Pass shape and partial-sum tiles of the paired reverse passes through S
+// Pass shape and partial-sum slots of the paired reverse passes through S
 // steps, reading even states `every` slots apart.
 struct PairPlan {
+    int tile_depth;  // steps per pass on resident tiles (0: streamed pairs)
     int cpl, depth, seg;
-    long long need;  // tiles of the widest tiling
+    long long need;  // partial-sum slots of the widest tiling
 };
 
 int plan_pairs(const rdcnn_sim *h, long long S, int every, const char *who, PairPlan *pl)
@@ -879,15 +900,23 @@ int plan_pairs(const rdcnn_sim *h, long long S, int every, const char *who, Pair
     // An odd S starts with one plain reverse step (state s_{S-1} is even);
     // then paired passes of `depth` steps and one shorter even remainder.
     const long long even = S & ~1LL;
+    const int tile_depth = h->adj_depth == 0 ? rd::tile_adjoint_depth(h->R, h->C, even) : 0;
+    if (tile_depth > 0) depth = tile_depth;
     const int klast = even == 0 ? 0 : (int)(even % depth == 0 ? depth : even % depth);
     long long need = 0;
     for (int k : {(S & 1) ? 1 : 0, (int)(even < depth ? even : depth), klast}) {
         if (k == 0) continue;
+        if (tile_depth > 0 && k > 1) {
+            const long long slots = rd::tile_adjoint_slots(h->R, h->C, k);
+            if (slots > need) need = slots;
+            continue;
+        }
         rd::StreamGeom gk;
         if (!rd::stream_geometry(h->R, h->C, cpl, k, seg, &gk))
             return fail(RDCNN_EINVAL, "%s: cannot tile %dx%d", who, h->R, h->C);
         if (gk.ntiles > need) need = gk.ntiles;
     }
+    pl->tile_depth = tile_depth;
     pl->cpl = cpl;
     pl->depth = depth;
     pl->seg = seg;
@@ -899,14 +928,14 @@ int plan_pairs(const rdcnn_sim *h, long long S, int every, const char *who, Pair
 // (state s_{t0+2i} at states + i * every states), ping-ponging (lam, mu)
 // between pp's two pairs of planes; the per-tile sums go to `partial` (need
 // tiles, zeroed here) and are folded into dtheta.
-// zero / fold: clear the partials first / fold them into dtheta at the end
-// (a chain of segments clears once and folds once).
+// whole: clear the partials first, leave (lam, mu) in pp's first pair and fold
+// the partials into dtheta at the end (a chain of segments does each once).
 int run_pairs(rdcnn_sim *h, const float *states, int every, long long S, Pingpong &pp,
               const PairPlan &pl, double *partial, double *dtheta, const char *who,
-              bool zero = true, bool fold = true)
+              bool whole = true)
 {
     hipError_t e = hipSuccess;
-    if (zero) e = rd::launch_zero(partial, rd::kAdjSums * pl.need, h->stream);
+    if (whole) e = rd::launch_zero(partial, rd::kAdjSums * pl.need, h->stream);
     if (e != hipSuccess) return hip_fail(e, who);
     const bool lam_sums = (h->grad_mask & kLamSumGrads) != 0;
     const long long even = S & ~1LL;
@@ -921,18 +950,25 @@ int run_pairs(rdcnn_sim *h, const float *states, int every, long long S, Pingpon
     }
     for (long long t_top = even; t_top > 0;) {
         const int k = (int)(t_top < pl.depth ? t_top : pl.depth);
-        rd::StreamGeom geom;
-        if (!rd::stream_geometry(h->R, h->C, pl.cpl, k, pl.seg, &geom))
-            return fail(RDCNN_EINVAL, "%s: cannot tile %dx%d", who, h->R, h->C);
-        e = rd::launch_adjoint_pair(pp.io(), states, every, t_top, h->R, h->C, h->bc, h->g, geom,
-                                    partial, lam_sums, h->stream);
+        if (pl.tile_depth > 0) {
+            e = rd::launch_tile_adjoint(pp.io(), states, every, t_top, h->R, h->C, h->bc, h->g,
+                                        rd::tile_adjoint_shape(h->R, h->C, k), partial, lam_sums,
+                                        h->stream);
+        } else {
+            rd::StreamGeom geom;
+            if (!rd::stream_geometry(h->R, h->C, pl.cpl, k, pl.seg, &geom))
+                return fail(RDCNN_EINVAL, "%s: cannot tile %dx%d", who, h->R, h->C);
+            e = rd::launch_adjoint_pair(pp.io(), states, every, t_top, h->R, h->C, h->bc, h->g, geom,
+                                        partial, lam_sums, h->stream);
+        }
         if (e != hipSuccess) return hip_fail(e, who);
         pp.flip();
         t_top -= k;
     }
+    if (!whole) return RDCNN_OK;
     e = pp.copy_back((size_t)h->R * h->C, h->stream);
-    if (e != hipSuccess) return hip_fail(e, who);
-    if (fold) e = rd::launch_adjoint_finish(partial, (int)pl.need, h->g, h->grad_mask, dtheta, h->stream);
+    if (e == hipSuccess)
+        e = rd::launch_adjoint_finish(partial, (int)pl.need, h->g, h->grad_mask, dtheta, h->stream);
     if (e != hipSuccess) return hip_fail(e, who);
     return RDCNN_OK;
 }
@@ -1137,7 +1173,8 @@ int rdcnn_step_bwd_ckpt(rdcnn_t h, const float *ckpt_dev, long long T, long long
     int cpl, depth, seg;
     if (!even_record_shape(h, 2, &cpl, &depth, &seg))
         return fail(RDCNN_EINVAL, "%s: grid too large to record", who);
-    // The recompute shares the GPU with the reverse passes of the next
+    const bool tiles = h->kind != 2 && rd::tile_record_depth(h->R, h->C, Smax) > 0;
+    // A streamed recompute shares the GPU with the reverse passes of the next
     // segment, so it aims at ~940 wavefronts, a third of what a recording run
     // alone aims at (taller segments, less halo work; never shorter ones than
     // alone), in passes of 6 steps.  On 1024^2, T = 2000 (22 strips: 24-row
@@ -1176,18 +1213,25 @@ int rdcnn_step_bwd_ckpt(rdcnn_t h, const float *ckpt_dev, long long T, long long
     if (e == hipSuccess) e = hipStreamWaitEvent(h->side, start, 0);  // the caller's earlier work
     if (e != hipSuccess) return hip_fail(e, who);
     float *segbuf[2] = {work_dev, work_dev + (size_t)(Smax + 1) * state};
+    // The reverse passes of all segments ping-pong between (lam, mu) and the
+    // first buffer's slot Smax, which no recompute writes: states go to slots
+    // below it, and each segment's final state, which nothing reads, to the
+    // second buffer's slot Smax.  Copying (lam, mu) back after each segment
+    // with an odd number of passes cost 11 us at 1024^2.
+    float *ws = segbuf[0] + (size_t)Smax * state, *unread = segbuf[1] + (size_t)Smax * state;
+    Pingpong pp(lam_dev, mu_dev, ws, ws + n);
     for (long long idx = 0; idx < nseg; ++idx) {
         const long long k = nseg - 1 - idx;
         const long long L = k == nseg - 1 ? Llast : S;
         const int b = (int)(idx & 1);
         float *traj = segbuf[b];
         // Recompute segment k on the side stream once the reverse pass that
-        // read this buffer two segments ago is done; its final state goes to
-        // slot L, the reverse passes' workspace (never read as a state).
+        // read this buffer two segments ago is done.
         if (idx >= 2 && (e = hipStreamWaitEvent(h->side, done[b], 0)) != hipSuccess)
             return hip_fail(e, who);
-        rc = record_even_chain(h, ckpt_dev + (size_t)k * state, L, traj, 2, traj + (size_t)L * state,
-                               cpl, depth, seg, h->side, who);
+        rc = record_even_chain(h, ckpt_dev + (size_t)k * state, L, traj, 2, unread,
+                               tiles ? rd::tile_record_depth(h->R, h->C, L) : 0, cpl, depth, seg,
+                               h->side, who);
         if (rc != RDCNN_OK) return rc;
         if ((e = hipEventRecord(ready[b], h->side)) != hipSuccess ||
             (e = hipStreamWaitEvent(h->stream, ready[b], 0)) != hipSuccess)
@@ -1196,13 +1240,14 @@ int rdcnn_step_bwd_ckpt(rdcnn_t h, const float *ckpt_dev, long long T, long long
         // recompute of segment k-1.
         PairPlan plk;
         if ((rc = plan_pairs(h, L, 2, who, &plk)) != RDCNN_OK) return rc;
-        float *ws = traj + (size_t)L * state;
-        Pingpong pp(lam_dev, mu_dev, ws, ws + n);
-        rc = run_pairs(h, traj, 2, L, pp, plk, h->partial, dtheta_accum, who, false, false);
+        rc = run_pairs(h, traj, 2, L, pp, plk, h->partial, dtheta_accum, who, false);
         if (rc != RDCNN_OK) return rc;
         if ((e = hipEventRecord(done[b], h->stream)) != hipSuccess) return hip_fail(e, who);
     }
-    e = rd::launch_adjoint_finish(h->partial, (int)need, h->g, h->grad_mask, dtheta_accum, h->stream);
+    e = pp.copy_back(n, h->stream);
+    if (e == hipSuccess)
+        e = rd::launch_adjoint_finish(h->partial, (int)need, h->g, h->grad_mask, dtheta_accum,
+                                      h->stream);
     if (e != hipSuccess) return hip_fail(e, who);
     return RDCNN_OK;
 }

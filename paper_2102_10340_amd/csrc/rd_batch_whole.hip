@@ -80,35 +80,13 @@ __device__ __forceinline__ void whole_body(const BatchInst &I, const float *in, 
         buf_load<CPL>(iu, vo, (unsigned)i * rowb, x[i + 1].u);
         buf_load<CPL>(iv, vo, (unsigned)i * rowb, x[i + 1].v);
     }
-    using V = vecf<CPL>;
-    const int W = (int)blockDim.y, plane = 2 * W * 64;
-    V *sm = (V *)smem + hl;
-    V *own = sm + b * 64;
-    const V *above = b == 0 ? (PERIODIC ? sm + (nb - 1) * 64 + 32 : own) : sm + (b - 1) * 64 + 32;
-    const V *below = b >= nb - 1 ? (PERIODIC ? sm : own + 32) : sm + (b + 1) * 64;
-    auto put = [&](int buf, int side, const Row<CPL> &r) __attribute__((always_inline)) {
-        V a, c;
-#pragma unroll
-        for (int e = 0; e < CPL; ++e) {
-            a[e] = r.u[e];
-            c[e] = r.v[e];
-        }
-        own[buf * 2 * plane + side * 32] = a;
-        own[buf * 2 * plane + plane + side * 32] = c;
-    };
-    auto get = [&](int buf, const V *p) __attribute__((always_inline)) {
-        Row<CPL> r;
-        const V a = p[buf * 2 * plane], c = p[buf * 2 * plane + plane];
-#pragma unroll
-        for (int e = 0; e < CPL; ++e) {
-            r.u[e] = a[e];
-            r.v[e] = c[e];
-        }
-        return r;
-    };
+    const int W = (int)blockDim.y;
+    const BlockLds<CPL> lds(smem, W, b, b == 0 ? nb - 1 : b - 1, b >= nb - 1 ? 0 : b + 1);
+    const auto *above = !PERIODIC && b == 0 ? lds.own : lds.above;
+    const auto *below = !PERIODIC && b >= nb - 1 ? lds.own + 32 : lds.below;
     Edge E[RW];
-    put(0, 0, x[1]);
-    put(0, 1, x[RW]);
+    lds.put(0, 0, x[1]);
+    lds.put(0, 1, x[RW]);
 #pragma unroll
     for (int i = 0; i < RW; ++i) E[i] = edges(x[i + 1]);
     lds_barrier();
@@ -116,14 +94,14 @@ __device__ __forceinline__ void whole_body(const BatchInst &I, const float *in, 
     const bool on = 2 * __builtin_amdgcn_readfirstlane((int)threadIdx.y) < nb;
     auto even_step = [&]() __attribute__((always_inline)) {
         if (on) {
-            const Row<CPL> nN = get(0, above), nS = get(0, below);
+            const Row<CPL> nN = lds.get(0, above), nS = lds.get(0, below);
 #pragma unroll
             for (int i = 0; i < RW; ++i) {
                 row_update<ModelFHN, CPL>(g, i == 0 ? nN : x[i], x[i + 1],
                                           i == RW - 1 ? nS : x[i + 2 > RW ? RW : i + 2],
                                           ghost(x[i + 1], E[i]), x[i]);
-                if (i == 0) put(1, 0, x[0]);
-                if (i == RW - 1) put(1, 1, x[RW - 1]);
+                if (i == 0) lds.put(1, 0, x[0]);
+                if (i == RW - 1) lds.put(1, 1, x[RW - 1]);
                 E[i] = edges(x[i]);
             }
         }
@@ -131,13 +109,13 @@ __device__ __forceinline__ void whole_body(const BatchInst &I, const float *in, 
     };
     auto odd_step = [&]() __attribute__((always_inline)) {
         if (on) {
-            const Row<CPL> nS = get(1, below), nN = get(1, above);
+            const Row<CPL> nS = lds.get(1, below), nN = lds.get(1, above);
 #pragma unroll
             for (int i = RW - 1; i >= 0; --i) {
                 row_update<ModelFHN, CPL>(g, i == 0 ? nN : x[i < 1 ? 0 : i - 1], x[i],
                                           i == RW - 1 ? nS : x[i + 1], ghost(x[i], E[i]), x[i + 1]);
-                if (i == RW - 1) put(0, 1, x[RW]);
-                if (i == 0) put(0, 0, x[1]);
+                if (i == RW - 1) lds.put(0, 1, x[RW]);
+                if (i == 0) lds.put(0, 0, x[1]);
                 E[i] = edges(x[i + 1]);
             }
         }

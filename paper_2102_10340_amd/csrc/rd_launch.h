@@ -97,8 +97,19 @@ struct TilePlan {
 // The fastest plan by the launcher's cost model; false if the grid is for the
 // streamed kernel.
 bool tile_plan(int R, int C, long long T, TilePlan *plan);
+// Recording passes: the (even) depth of the passes of an n-step run, 0 if the
+// grid is for the streamed kernel; the shape of a pass of K steps.
+int tile_record_depth(int R, int C, long long n);
+TileShape tile_shape(int R, int C, int K);
+// Where a recording pass puts the states of its even levels: level j to at +
+// (j / 2) * every * 2*R*C floats, level 0 only if `first`.
+struct TileRecord {
+    float *at;
+    int every;
+    bool first;
+};
 hipError_t launch_tile(const float *in, float *out, int R, int C, int bc, const Gene &g,
-                       const TileShape &shape, hipStream_t s);
+                       const TileShape &shape, hipStream_t s, const TileRecord *rec = nullptr);
 hipError_t launch_tile_gs(const float *in, float *out, int R, int C, int bc, const float *params,
                           const TileShape &shape, hipStream_t s);
 
@@ -142,6 +153,20 @@ hipError_t launch_adjoint(const AdjPlanes &io, const float *states, int every, l
 hipError_t launch_adjoint_pair(const AdjPlanes &io, const float *even_states, int every,
                                long long t_top, int R, int C, int bc, const Gene &g,
                                const StreamGeom &geom, double *partial, bool lam_sums,
+                               hipStream_t s);
+
+// The same on resident tiles (rd_tile_adj.h): the (even) depth of the passes
+// through S steps, 0 if the grid is for the streamed pairs; the shape of a pass
+// of K steps and the partial-sum slots it uses (one per wavefront of a tile).
+// Limit: us per reverse step, resident against streamed, 1024^2 2.81 / 3.95,
+// 1500^2 5.98 / 6.05.
+constexpr long long kMaxTileAdjCells = 2200000;
+int tile_adjoint_depth(int R, int C, long long S);
+TileShape tile_adjoint_shape(int R, int C, int K);
+long long tile_adjoint_slots(int R, int C, int K);
+hipError_t launch_tile_adjoint(const AdjPlanes &io, const float *even_states, int every,
+                               long long t_top, int R, int C, int bc, const Gene &g,
+                               const TileShape &shape, double *partial, bool lam_sums,
                                hipStream_t s);
 
 hipError_t launch_zero(double *p, long long n, hipStream_t s);

@@ -44,36 +44,100 @@ double pass_us(int R, int C, int cpl, int rw, int w, int K, int ntiles)
     return 3.57 + odd + mb / 11.0 + rounds * K * step / 2400.0;
 }
 
+// The same for a paired reverse pass, fitted to 280 timed passes on 128^2 to
+// 1500^2 (7 % rms; the picked shape within 2 % of the fastest timed one).
+double adj_pass_us(int R, int C, int cpl, int rw, int w, int K, int ntiles)
+{
+    constexpr int kVgpr[2][5] = {{0, 0, 108, 127, 146}, {0, 0, 168, 203, 242}};
+    const int vg = (kVgpr[cpl == 4][rw] + 7) / 8 * 8;
+    int occ = 512 / vg * 4 / w;
+    if (occ < 1) occ = 1;
+    const int per = (ntiles + kCus - 1) / kCus, rounds = (per + occ - 1) / occ;
+    const double conc = (double)per / rounds;
+    double rest = (double)(K - 1) / (2 * rw) - 1.0;
+    if (rest < 0.0) rest = 0.0;
+    const double act = (w - rest) * conc;
+    const double ins = 31.0 * cpl * rw;
+    double step = act / 4 * ins * 1.87;
+    if (step < ins * 4.76) step = ins * 4.76;
+    step += 1.09 * 4 * cpl * act + 1455;
+    const double mb = ((double)ntiles * (2 * w * rw) * 32 * cpl * 8 + 8.0 * R * C) * 1e-6;
+    const double odd = C % cpl ? 1.2 + 0.02 * ntiles / kCus * cpl * cpl : 0.0;
+    return 2.93 + odd + mb / 3.42 + rounds * K * step / 2400.0;
+}
+
 struct Table {
     int R = -1, C = -1;
     TileShape best[kMaxTileDepth + 1];
     double us[kMaxTileDepth + 1];
 };
 
-// Fastest shape for each pass depth on an R x C grid.
-void fill_table(Table &tb, int R, int C)
+// Output columns of a tile, and tiles of an R x C grid (0: the shape has no output).
+int tile_out_cols(const TileShape &s)
+{
+    return 32 * s.cpl - 2 * ((s.K + s.cpl - 1) / s.cpl * s.cpl);
+}
+long long tiles_of(int R, int C, const TileShape &s)
+{
+    const int h = tile_out_rows(s), wout = tile_out_cols(s);
+    if (h < 1 || wout < 1) return 0;
+    return ((long long)C + wout - 1) / wout * (((long long)R + h - 1) / h);
+}
+
+// Fastest shape for each pass depth on an R x C grid (adj: of the reverse
+// passes, whose depths are even).
+void fill_table(Table &tb, int R, int C, bool adj)
 {
     tb.R = R;
     tb.C = C;
     for (int K = 1; K <= kMaxTileDepth; ++K) {
         tb.us[K] = INFINITY;
-        for (int cpl = 2; cpl <= 4; cpl += 2) {
-            const int kpad = (K + cpl - 1) / cpl * cpl, wout = 32 * cpl - 2 * kpad;
-            const long long nstrips = ((long long)C + wout - 1) / wout;
-            for (int rw = cpl / 2; rw <= 6; ++rw)
+        tb.best[K] = TileShape{0, 0, 0, 0};
+        if (adj && ((K & 1) || K > 12)) continue;
+        for (int cpl = 2; cpl <= 4; cpl += 2)
+            for (int rw = adj ? 2 : cpl / 2; rw <= (adj ? 4 : 6); ++rw)
                 for (int w : kWaves) {
-                    const int h = 2 * w * rw - 2 * K;
-                    if (h < 1) continue;
-                    const long long nt = nstrips * (((long long)R + h - 1) / h);
-                    if (nt > 1 << 22) continue;
-                    const double us = pass_us(R, C, cpl, rw, w, K, (int)nt);
+                    if (adj && w > 8) break;
+                    const TileShape sh{cpl, rw, w, K};
+                    const long long nt = tiles_of(R, C, sh);
+                    if (nt < 1 || nt > 1 << 22) continue;
+                    const double us = (adj ? adj_pass_us : pass_us)(R, C, cpl, rw, w, K, (int)nt);
                     if (us < tb.us[K]) {
                         tb.us[K] = us;
-                        tb.best[K] = TileShape{cpl, rw, w, K};
+                        tb.best[K] = sh;
                     }
                 }
+    }
+}
+
+// The tables of the last grid size, per thread (a program that makes a handle
+// per call fills them once).
+const Table &table(int R, int C, bool adj)
+{
+    static thread_local Table tb[2];
+    Table &t = tb[adj];
+    if (t.R != R || t.C != C) fill_table(t, R, C, adj);
+    return t;
+}
+
+// The even depth of the passes through S steps with the least total time: of
+// each number of passes, equally deep ones.
+int even_depth(const Table &tb, long long S)
+{
+    int best = 2;
+    double least = INFINITY;
+    for (int K = 2; K <= kMaxTileDepth; K += 2) {
+        const long long n = (S + K - 1) / K;
+        int d = (int)((S + n - 1) / n);
+        d += d & 1;
+        const int last = (int)(S - (n - 1) * d);  // > 0: d <= K
+        const double us = (double)(n - 1) * tb.us[d] + tb.us[last + (last & 1)];
+        if (us < least) {
+            least = us;
+            best = d;
         }
     }
+    return best;
 }
 
 }  // namespace
@@ -84,10 +148,7 @@ bool tile_plan(int R, int C, long long T, TilePlan *plan)
     // kernel's wider strips waste less on halos and hide their memory traffic
     // behind the arithmetic.
     if ((long long)R * C > kMaxTileCells || T < 1) return false;
-    // the last grid size's table, per thread (a program that makes a handle per
-    // call fills it once)
-    static thread_local Table tb;
-    if (tb.R != R || tb.C != C) fill_table(tb, R, C);
+    const Table &tb = table(R, C, false);
     double best = INFINITY;
     for (int K = 1; K <= kMaxTileDepth; ++K) {
         const long long n = (T + K - 1) / K;  // passes, of two depths that differ by one
@@ -105,33 +166,52 @@ bool tile_plan(int R, int C, long long T, TilePlan *plan)
     return best < INFINITY;
 }
 
+int tile_record_depth(int R, int C, long long n)
+{
+    if ((long long)R * C > kMaxTileCells || n < 1) return 0;
+    return even_depth(table(R, C, false), n);
+}
+
+TileShape tile_shape(int R, int C, int K) { return table(R, C, false).best[K]; }
+
+int tile_adjoint_depth(int R, int C, long long S)
+{
+    if ((long long)R * C > kMaxTileAdjCells || S < 2) return 0;
+    return even_depth(table(R, C, true), S);
+}
+
+TileShape tile_adjoint_shape(int R, int C, int K) { return table(R, C, true).best[K]; }
+
+long long tile_adjoint_slots(int R, int C, int K)
+{
+    const TileShape sh = tile_adjoint_shape(R, C, K);
+    return tiles_of(R, C, sh) * sh.w;
+}
+
 namespace {
 
-template <class M>
-hipError_t launch_as(TileFn<M> f, const float *in, float *out, int R, int C, int bc,
-                     const typename M::Params &p, const TileShape &sh, hipStream_t s)
+// The tiling of a pass; false if the shape has no output or too many tiles.
+bool tile_geometry(int R, int C, int bc, const TileShape &sh, TileArgs *t)
 {
-    const int kpad = (sh.K + sh.cpl - 1) / sh.cpl * sh.cpl;
-    TileStepArgsT<M> a;
-    a.t.R = R;
-    a.t.C = C;
-    a.t.bc = bc;
-    a.t.kpad = kpad;
-    a.t.wout = 32 * sh.cpl - 2 * kpad;
-    a.t.h = tile_out_rows(sh);
-    if (!f || a.t.wout < 1 || a.t.h < 1 || sh.K < 1 || sh.w < 1 || sh.w > 16)
-        return hipErrorInvalidValue;
-    if (a.t.h > R) a.t.h = R;
-    a.t.nsegs = (R + a.t.h - 1) / a.t.h;
-    const long long nt = ((long long)C + a.t.wout - 1) / a.t.wout * a.t.nsegs;
-    if (nt > 1 << 28) return hipErrorInvalidValue;
-    a.t.ntiles = (int)nt;
-    a.t.per_xcd = (a.t.ntiles + 7) / 8;
-    a.t.vec_ok = C % sh.cpl == 0;
-    a.in = in;
-    a.out = out;
-    a.g = p;
-    a.K = sh.K;
+    const long long nt = tiles_of(R, C, sh);
+    if (sh.K < 1 || sh.w < 1 || sh.w > 16 || nt < 1 || nt > 1 << 28) return false;
+    t->R = R;
+    t->C = C;
+    t->bc = bc;
+    t->wout = tile_out_cols(sh);
+    t->kpad = (32 * sh.cpl - t->wout) / 2;
+    t->h = tile_out_rows(sh) < R ? tile_out_rows(sh) : R;
+    t->nsegs = (R + t->h - 1) / t->h;
+    t->ntiles = (int)nt;
+    t->per_xcd = (t->ntiles + 7) / 8;
+    t->vec_ok = C % sh.cpl == 0;
+    return true;
+}
+
+template <class Args>
+hipError_t launch_tiles(void (*f)(Args), const Args &a, const TileShape &sh, hipStream_t s)
+{
+    if (!f) return hipErrorInvalidValue;
     const int lds = tile_lds_bytes(sh.cpl, sh.w);
     if (lds > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute((const void *)f,
@@ -145,16 +225,53 @@ hipError_t launch_as(TileFn<M> f, const float *in, float *out, int R, int C, int
 }  // namespace
 
 hipError_t launch_tile(const float *in, float *out, int R, int C, int bc, const Gene &g,
-                       const TileShape &shape, hipStream_t s)
+                       const TileShape &sh, hipStream_t s, const TileRecord *rec)
 {
-    return launch_as<ModelFHN>(tile_fn_fhn(shape.cpl, shape.rw), in, out, R, C, bc, g, shape, s);
+    TileStepArgsT<ModelFHN> a;
+    if (!tile_geometry(R, C, bc, sh, &a.t)) return hipErrorInvalidValue;
+    a.in = in;
+    a.out = out;
+    a.g = g;
+    a.K = sh.K;
+    a.rec = rec ? rec->at : nullptr;
+    a.rec_stride = rec ? 8u * (unsigned)rec->every * (unsigned)R * (unsigned)C : 0u;
+    a.rec_first = rec && rec->first;
+    return launch_tiles(rec ? tile_fn_rec(sh.cpl, sh.rw) : tile_fn_fhn(sh.cpl, sh.rw), a, sh, s);
 }
 
 hipError_t launch_tile_gs(const float *in, float *out, int R, int C, int bc, const float *params,
-                          const TileShape &shape, hipStream_t s)
+                          const TileShape &sh, hipStream_t s)
 {
-    const GrayScottParams p{params[0], params[1], params[2], params[3], params[4]};
-    return launch_as<ModelGrayScott>(tile_fn_gs(shape.cpl, shape.rw), in, out, R, C, bc, p, shape, s);
+    TileStepArgsT<ModelGrayScott> a;
+    if (!tile_geometry(R, C, bc, sh, &a.t)) return hipErrorInvalidValue;
+    a.in = in;
+    a.out = out;
+    a.g = GrayScottParams{params[0], params[1], params[2], params[3], params[4]};
+    a.K = sh.K;
+    a.rec = nullptr;
+    a.rec_stride = 0;
+    a.rec_first = 0;
+    return launch_tiles(tile_fn_gs(sh.cpl, sh.rw), a, sh, s);
+}
+
+hipError_t launch_tile_adjoint(const AdjPlanes &io, const float *even_states, int every,
+                               long long t_top, int R, int C, int bc, const Gene &g,
+                               const TileShape &sh, double *partial, bool lam_sums, hipStream_t s)
+{
+    TileAdjArgs a;
+    if ((sh.K & 1) || (t_top & 1) || t_top < sh.K || every < 1 || sh.w > 8 ||
+        !tile_geometry(R, C, bc, sh, &a.t))
+        return hipErrorInvalidValue;
+    a.in_l = io.in_l;
+    a.in_m = io.in_m;
+    a.out_l = io.out_l;
+    a.out_m = io.out_m;
+    a.states = even_states + (t_top - sh.K) / 2 * every * 2LL * R * C;
+    a.state_stride = 8u * (unsigned)every * (unsigned)R * (unsigned)C;
+    a.g = g;
+    a.K = sh.K;
+    a.partial = partial;
+    return launch_tiles(tile_adj_fn(lam_sums, sh.cpl, sh.rw), a, sh, s);
 }
 
 }  // namespace rd

@@ -38,6 +38,11 @@ struct TileStepArgsT {
     float *out;
     typename M::Params g;
     int K;  // steps of the pass
+    // recording passes (they start at an even time): the state of even level j
+    // goes to rec + (j / 2) * rec_stride bytes, level 0 only if rec_first
+    float *rec;
+    unsigned rec_stride;
+    int rec_first;
 };
 
 // Barrier that orders LDS accesses only (global stores stay in flight).
@@ -126,26 +131,28 @@ struct HalfTile {
     }
 
     template <bool FAST>
-    __device__ __forceinline__ void load(const Buf &b, unsigned ro, float (&x)[CPL]) const
+    __device__ __forceinline__ void load(const Buf &b, unsigned ro, float (&x)[CPL],
+                                         unsigned soff = 0) const
     {
         if (FAST) {
-            buf_load<CPL>(b, vo + ro, 0, x);
+            buf_load<CPL>(b, vo + ro, soff, x);
         } else {
 #pragma unroll
-            for (int e = 0; e < CPL; ++e) x[e] = buf_load1(b, mo[e] + ro, 0);
+            for (int e = 0; e < CPL; ++e) x[e] = buf_load1(b, mo[e] + ro, soff);
         }
     }
 
     // output columns lie inside the grid, where vo is the lane's own column
     template <bool FAST>
-    __device__ __forceinline__ void store(const Buf &b, unsigned ro, int C, const float (&x)[CPL]) const
+    __device__ __forceinline__ void store(const Buf &b, unsigned ro, int C, const float (&x)[CPL],
+                                          unsigned soff = 0) const
     {
         if (FAST) {
-            buf_store<CPL>(b, vo + ro, 0, x);
+            buf_store<CPL>(b, vo + ro, soff, x);
         } else {
 #pragma unroll
             for (int e = 0; e < CPL; ++e)
-                if (cx + e < C) buf_store1(b, 4u * (unsigned)(cx + e) + ro, 0, x[e]);
+                if (cx + e < C) buf_store1(b, 4u * (unsigned)(cx + e) + ro, soff, x[e]);
         }
     }
 
@@ -160,10 +167,54 @@ struct HalfTile {
     }
 };
 
+// The LDS through which a lane's block trades rows with its neighbours:
+// [buffer][layer][block][first, last row][32 lanes] of CPL floats.
+template <int CPL>
+struct BlockLds {
+    using V = vecf<CPL>;
+    V *own;
+    const V *above, *below;  // last row of the block above, first row of the one below
+    int plane;
+
+    // block b of 2 * waves; bn, bs: the blocks above and below it
+    __device__ __forceinline__ BlockLds(char *smem, int waves, int b, int bn, int bs)
+    {
+        V *sm = (V *)smem + ((int)threadIdx.x & 31);
+        own = sm + b * 64;
+        above = sm + bn * 64 + 32;
+        below = sm + bs * 64;
+        plane = 2 * waves * 64;
+    }
+
+    __device__ __forceinline__ void put(int buf, int side, const Row<CPL> &r) const
+    {
+        V a, c;
+#pragma unroll
+        for (int e = 0; e < CPL; ++e) {
+            a[e] = r.u[e];
+            c[e] = r.v[e];
+        }
+        own[buf * 2 * plane + side * 32] = a;
+        own[buf * 2 * plane + plane + side * 32] = c;
+    }
+
+    __device__ __forceinline__ Row<CPL> get(int buf, const V *p) const
+    {
+        Row<CPL> r;
+        const V a = p[buf * 2 * plane], c = p[buf * 2 * plane + plane];
+#pragma unroll
+        for (int e = 0; e < CPL; ++e) {
+            r.u[e] = a[e];
+            r.v[e] = c[e];
+        }
+        return r;
+    }
+};
+
 // LDS bytes of a workgroup: [buffer][layer][block][first, last row][32 lanes].
 constexpr int tile_lds_bytes(int cpl, int w) { return 2 * 2 * (2 * w) * 2 * 32 * 4 * cpl; }
 
-template <class M, int CPL, int RW, bool FAST>
+template <class M, int CPL, int RW, bool FAST, bool REC>
 __device__ __forceinline__ void tile_body(const TileStepArgsT<M> &A, int x0, int y0, int y1, char *smem)
 {
     const int C = A.t.C, R = A.t.R, bc = A.t.bc, K = A.K;
@@ -199,37 +250,12 @@ __device__ __forceinline__ void tile_body(const TileStepArgsT<M> &A, int x0, int
             t.unmirror(x[i].v);
         }
     }
-    using V = vecf<CPL>;
     const int b = 2 * w + half;
-    const int plane = 2 * W * 64;
-    V *sm = (V *)smem + (lane & 31);
-    V *own = sm + b * 64;
-    const V *above = sm + max(b - 1, 0) * 64 + 32;         // last row of the block above
-    const V *below = sm + min(b + 1, 2 * W - 1) * 64;      // first row of the block below
-    auto put = [&](int buf, int side, const Row<CPL> &r) __attribute__((always_inline)) {
-        V a, c;
-#pragma unroll
-        for (int e = 0; e < CPL; ++e) {
-            a[e] = r.u[e];
-            c[e] = r.v[e];
-        }
-        own[buf * 2 * plane + side * 32] = a;
-        own[buf * 2 * plane + plane + side * 32] = c;
-    };
-    auto get = [&](int buf, const V *p) __attribute__((always_inline)) {
-        Row<CPL> r;
-        const V a = p[buf * 2 * plane], c = p[buf * 2 * plane + plane];
-#pragma unroll
-        for (int e = 0; e < CPL; ++e) {
-            r.u[e] = a[e];
-            r.v[e] = c[e];
-        }
-        return r;
-    };
+    const BlockLds<CPL> lds(smem, W, b, max(b - 1, 0), min(b + 1, 2 * W - 1));
     // Edge columns of each row, fetched as soon as the row is made.
     Edge E[RW];
-    put(0, 0, x[1]);
-    put(0, 1, x[RW]);
+    lds.put(0, 0, x[1]);
+    lds.put(0, 1, x[RW]);
 #pragma unroll
     for (int i = 0; i < RW; ++i) E[i] = edge_of(x[i + 1]);
     lds_barrier();
@@ -237,13 +263,13 @@ __device__ __forceinline__ void tile_body(const TileStepArgsT<M> &A, int x0, int
     auto active = [&](int s) { return q0 + 2 * RW > s + 1 && q0 < H - s - 1; };
     auto even_step = [&](int s) __attribute__((always_inline)) {
         if (active(s)) {
-            const Row<CPL> nN = get(0, above), nS = get(0, below);
+            const Row<CPL> nN = lds.get(0, lds.above), nS = lds.get(0, lds.below);
 #pragma unroll
             for (int i = 0; i < RW; ++i) {
                 row_update<M, CPL>(g, i == 0 ? nN : x[i], x[i + 1],
                                    i == RW - 1 ? nS : x[i + 2 > RW ? RW : i + 2], E[i], x[i]);
-                if (i == 0) put(1, 0, x[0]);
-                if (i == RW - 1) put(1, 1, x[RW - 1]);
+                if (i == 0) lds.put(1, 0, x[0]);
+                if (i == RW - 1) lds.put(1, 1, x[RW - 1]);
                 E[i] = edge_of(x[i]);
             }
         }
@@ -251,19 +277,20 @@ __device__ __forceinline__ void tile_body(const TileStepArgsT<M> &A, int x0, int
     };
     auto odd_step = [&](int s) __attribute__((always_inline)) {
         if (active(s)) {
-            const Row<CPL> nS = get(1, below), nN = get(1, above);
+            const Row<CPL> nS = lds.get(1, lds.below), nN = lds.get(1, lds.above);
 #pragma unroll
             for (int i = RW - 1; i >= 0; --i) {
                 row_update<M, CPL>(g, i == 0 ? nN : x[i < 1 ? 0 : i - 1], x[i],
                                    i == RW - 1 ? nS : x[i + 1], E[i], x[i + 1]);
-                if (i == RW - 1) put(0, 1, x[RW]);
-                if (i == 0) put(0, 0, x[1]);
+                if (i == RW - 1) lds.put(0, 1, x[RW]);
+                if (i == 0) lds.put(0, 0, x[1]);
                 E[i] = edge_of(x[i + 1]);
             }
         }
         lds_barrier();
     };
-    auto store = [&](auto slot0) __attribute__((always_inline)) {
+    auto store = [&](const Buf &bu, const Buf &bv, unsigned soff, auto slot0)
+        __attribute__((always_inline)) {
         if (!t.lane_out) return;
         const int r0 = half ? rb : ra;
 #pragma unroll
@@ -271,24 +298,33 @@ __device__ __forceinline__ void tile_body(const TileStepArgsT<M> &A, int x0, int
             const int r = r0 + i;
             if (r >= y0 && r < y1) {
                 const unsigned ro = 4u * (unsigned)r * (unsigned)C;
-                t.template store<FAST>(ou, ro, C, x[i + decltype(slot0)::value].u);
-                t.template store<FAST>(ov, ro, C, x[i + decltype(slot0)::value].v);
+                t.template store<FAST>(bu, ro, C, x[i + decltype(slot0)::value].u, soff);
+                t.template store<FAST>(bv, ro, C, x[i + decltype(slot0)::value].v, soff);
             }
         }
     };
+    const Buf ru(REC ? A.rec : A.in, REC ? (unsigned)((K - 1) / 2) * A.rec_stride + pbytes : 0u);
+    const Buf rv(REC ? A.rec + (size_t)R * C : A.in,
+                 REC ? (unsigned)((K - 1) / 2) * A.rec_stride + pbytes : 0u);
+    auto record = [&](int s) __attribute__((always_inline)) {
+        if (REC && (s > 0 || A.rec_first))
+            store(ru, rv, (unsigned)(s / 2) * A.rec_stride, std::integral_constant<int, 1>{});
+    };
     for (int s = 0; s + 2 <= K; s += 2) {
+        record(s);
         even_step(s);
         odd_step(s + 1);
     }
     if (K & 1) {
+        record(K - 1);
         even_step(K - 1);
-        store(std::integral_constant<int, 0>{});
+        store(ou, ov, 0u, std::integral_constant<int, 0>{});
     } else {
-        store(std::integral_constant<int, 1>{});
+        store(ou, ov, 0u, std::integral_constant<int, 1>{});
     }
 }
 
-template <class M, int CPL, int RW>
+template <class M, int CPL, int RW, bool REC>
 __global__ __launch_bounds__(1024) void tile_step_kernel(TileStepArgsT<M> A)
 {
     extern __shared__ __align__(16) char tile_smem[];
@@ -297,34 +333,38 @@ __global__ __launch_bounds__(1024) void tile_step_kernel(TileStepArgsT<M> A)
     const int strip = tl / A.t.nsegs, seg = tl - strip * A.t.nsegs;
     const int x0 = strip * A.t.wout - A.t.kpad, y0 = seg * A.t.h, y1 = min(y0 + A.t.h, A.t.R);
     if (A.t.vec_ok || (x0 >= 0 && x0 + 32 * CPL <= A.t.C))
-        tile_body<M, CPL, RW, true>(A, x0, y0, y1, tile_smem);
+        tile_body<M, CPL, RW, true, REC>(A, x0, y0, y1, tile_smem);
     else
-        tile_body<M, CPL, RW, false>(A, x0, y0, y1, tile_smem);
+        tile_body<M, CPL, RW, false, REC>(A, x0, y0, y1, tile_smem);
 }
 
 template <class M>
 using TileFn = void (*)(TileStepArgsT<M>);
 
-template <class M, int CPL>
+// Instances: 2 columns per lane with blocks of 1 to 6 rows (one-row blocks only
+// pay on the smallest grids), 4 with 2 to 6.
+template <class M, int CPL, bool REC>
 TileFn<M> pick_tile_rows(int rw)
 {
-    if constexpr (CPL == 2) {  // one-row blocks only pay on the smallest grids
-        if (rw == 1) return &tile_step_kernel<M, CPL, 1>;
+    if constexpr (CPL == 2) {
+        if (rw == 1) return &tile_step_kernel<M, CPL, 1, REC>;
     }
     switch (rw) {
-        case 2: return &tile_step_kernel<M, CPL, 2>;
-        case 3: return &tile_step_kernel<M, CPL, 3>;
-        case 4: return &tile_step_kernel<M, CPL, 4>;
-        case 5: return &tile_step_kernel<M, CPL, 5>;
-        case 6: return &tile_step_kernel<M, CPL, 6>;
+        case 2: return &tile_step_kernel<M, CPL, 2, REC>;
+        case 3: return &tile_step_kernel<M, CPL, 3, REC>;
+        case 4: return &tile_step_kernel<M, CPL, 4, REC>;
+        case 5: return &tile_step_kernel<M, CPL, 5, REC>;
+        case 6: return &tile_step_kernel<M, CPL, 6, REC>;
         default: return nullptr;
     }
 }
 
-template <class M>
+template <class M, bool REC>
 TileFn<M> pick_tile(int cpl, int rw)
 {
-    return cpl == 2 ? pick_tile_rows<M, 2>(rw) : cpl == 4 ? pick_tile_rows<M, 4>(rw) : nullptr;
+    return cpl == 2   ? pick_tile_rows<M, 2, REC>(rw)
+           : cpl == 4 ? pick_tile_rows<M, 4, REC>(rw)
+                      : nullptr;
 }
 
 }  // namespace rd

@@ -1,6 +1,6 @@
-// Resident-tile kernel instances: FitzHugh-Nagumo (rd_tile_body.h).
+// Resident-tile kernel instances: FitzHugh-Nagumo, plain passes (rd_tile_body.h).
 #include "rd_tile.h"
 
 namespace rd {
-TileFn<ModelFHN> tile_fn_fhn(int cpl, int rw) { return pick_tile<ModelFHN>(cpl, rw); }
+TileFn<ModelFHN> tile_fn_fhn(int cpl, int rw) { return pick_tile<ModelFHN, false>(cpl, rw); }
 }  // namespace rd

@@ -2,5 +2,5 @@
 #include "rd_tile.h"
 
 namespace rd {
-TileFn<ModelGrayScott> tile_fn_gs(int cpl, int rw) { return pick_tile<ModelGrayScott>(cpl, rw); }
+TileFn<ModelGrayScott> tile_fn_gs(int cpl, int rw) { return pick_tile<ModelGrayScott, false>(cpl, rw); }
 }  // namespace rd
