@@ -227,6 +227,22 @@ int side_stream(hipStream_t *out, const char *who)
 
 }  // namespace
 
+namespace {
+
+// Whether p is plain device memory of the device that holds `ref`.
+bool on_device_of(const void *ref, const void *p)
+{
+    hipPointerAttribute_t a, b;
+    if (hipPointerGetAttributes(&a, ref) == hipSuccess &&
+        hipPointerGetAttributes(&b, p) == hipSuccess)
+        return a.type == hipMemoryTypeDevice && b.type == hipMemoryTypeDevice && a.device == b.device &&
+               !b.isManaged;
+    (void)hipGetLastError();  // an unregistered pointer is no error here
+    return false;
+}
+
+}  // namespace
+
 int rd::check_finite_state(const float *x, long long n, int **flag, hipStream_t s, const char *who)
 {
     if (!*flag) {
@@ -1275,9 +1291,19 @@ int rdcnn_read(rdcnn_t h, float *u_dst, float *v_dst, int dst_is_host)
     if (!h || !u_dst || !v_dst) return fail(RDCNN_EINVAL, "rdcnn_read: NULL argument");
     const size_t bytes = sizeof(float) * (size_t)h->R * h->C;
     const float *s = h->buf[h->cur];
-    const hipMemcpyKind kind = dst_is_host ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice;
-    hipError_t e = hipMemcpyAsync(u_dst, s, bytes, kind, h->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(v_dst, s + (size_t)h->R * h->C, bytes, kind, h->stream);
+    const size_t n = (size_t)h->R * h->C;
+    hipError_t e;
+    if (dst_is_host) {
+        e = hipMemcpyAsync(u_dst, s, bytes, hipMemcpyDeviceToHost, h->stream);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(v_dst, s + n, bytes, hipMemcpyDeviceToHost, h->stream);
+    } else if (on_device_of(s, u_dst) && on_device_of(s, v_dst)) {
+        e = rd::launch_copy_planes(s, (long long)n, u_dst, v_dst, h->stream);
+    } else {  // another device's memory, or the host's: the copies find their way
+        e = hipMemcpyAsync(u_dst, s, bytes, hipMemcpyDeviceToDevice, h->stream);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(v_dst, s + n, bytes, hipMemcpyDeviceToDevice, h->stream);
+    }
     if (e == hipSuccess && dst_is_host && !h->check_finite) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return hip_fail(e, "rdcnn_read");
     if (h->check_finite)

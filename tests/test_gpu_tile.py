@@ -66,3 +66,23 @@ def test_streamed_kernel_takes_the_larger_grids():
     sim = Simulation(torch.zeros((2500, 2500), device="cuda"), W.PLAIN_GENE, tuned=False)
     assert sim.pass_config()["kind"] == 2
     sim.close()
+
+
+@pytest.mark.parametrize("shape", [(1, 1), (7, 9), (64, 130), (300, 257)], ids=lambda s: "%dx%d" % s)
+def test_read_into_device_views(shape):
+    """A device read copies both planes in one launch, also to destinations that
+    are not 16-byte aligned, and leaves what lies beside them."""
+    from paper_2102_10340_amd import Simulation
+    R, C = shape
+    x = W.uniform_x(R, C, 3)
+    sim = Simulation(_t(x), W.PLAIN_GENE, tuned=False).step(3)
+    want = sim.state().clone()
+    for off in (0, 1, 4):
+        buf = torch.full((2, R * C + 8), 7.0, device="cuda")
+        u, v = (buf[k, off:off + R * C].view(R, C) for k in range(2))
+        sim.read_into(u, v)
+        assert torch.equal(u, want[0]) and torch.equal(v, want[1]), off
+        assert torch.all(buf[:, :off] == 7.0) and torch.all(buf[:, off + R * C:] == 7.0), off
+    got = sim.read()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    sim.close()
