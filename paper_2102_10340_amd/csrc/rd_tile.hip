@@ -17,8 +17,7 @@ constexpr int kWaves[] = {4, 6, 8, 10, 12, 16};
 
 // Predicted microseconds of one K-step pass.  Fitted to 1500 timed passes on
 // grids of 128^2 to 2048^2, 200x700 and 777x1301 (7 % rms); on each of them the
-// shape it picks is within 1.2 % of the fastest timed one, except where C is
-// odd.  The terms: launch and fill; the tile reads and the writes; then per
+// shape it picks is within 1.2 % of the fastest timed one.  The terms: launch and fill; the tile reads and the writes; then per
 // step the VALU work of the workgroups that share a compute unit (never less
 // than one wavefront's own issue), their LDS traffic, and the barrier.
 double pass_us(int R, int C, int cpl, int rw, int w, int K, int ntiles)
@@ -40,8 +39,7 @@ double pass_us(int R, int C, int cpl, int rw, int w, int K, int ntiles)
     if (step < ins * 5.5) step = ins * 5.5;
     step += 0.63 * 4 * cpl * act + 268;
     const double mb = ((double)ntiles * (2 * w * rw) * 32 * cpl * 8 + 8.0 * R * C) * 1e-6;
-    const double odd = C % cpl ? 1.2 + 0.02 * ntiles / kCus * cpl * cpl : 0.0;  // column-wise edge tiles
-    return 3.57 + odd + mb / 11.0 + rounds * K * step / 2400.0;
+    return 3.57 + mb / 11.0 + rounds * K * step / 2400.0;
 }
 
 // The same for a paired reverse pass, fitted to 280 timed passes on 128^2 to
@@ -62,8 +60,7 @@ double adj_pass_us(int R, int C, int cpl, int rw, int w, int K, int ntiles)
     if (step < ins * 4.76) step = ins * 4.76;
     step += 1.09 * 4 * cpl * act + 1455;
     const double mb = ((double)ntiles * (2 * w * rw) * 32 * cpl * 8 + 8.0 * R * C) * 1e-6;
-    const double odd = C % cpl ? 1.2 + 0.02 * ntiles / kCus * cpl * cpl : 0.0;
-    return 2.93 + odd + mb / 3.42 + rounds * K * step / 2400.0;
+    return 2.93 + mb / 3.42 + rounds * K * step / 2400.0;
 }
 
 struct Table {

@@ -32,7 +32,7 @@ struct TileAdjArgs {
     double *partial;        // [>= ntiles * wavefronts][NSUM], accumulated
 };
 
-template <int CPL, int RW, bool FAST, bool LAMS>
+template <int CPL, int RW, bool SPLIT, bool LAMS>
 __device__ __forceinline__ void tile_adjoint_body(const TileAdjArgs &A, int tile, int x0, int y0, int y1,
                                                   char *smem)
 {
@@ -46,7 +46,7 @@ __device__ __forceinline__ void tile_adjoint_body(const TileAdjArgs &A, int tile
     const int W = (int)blockDim.y;
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
     const int lane = (int)threadIdx.x, half = lane >> 5;
-    HalfTile<CPL> t;
+    HalfTile<CPL, SPLIT> t;
     t.setup(A.t, x0);
     const int q0 = 2 * w * RW;
     const int ra = y0 - K + q0, rb = ra + RW;
@@ -66,18 +66,18 @@ __device__ __forceinline__ void tile_adjoint_body(const TileAdjArgs &A, int tile
             const unsigned so = (unsigned)(P - 1 - p) * A.state_stride;
 #pragma unroll
             for (int i = 0; i < RW + 2; ++i) {
-                t.template load<FAST>(sb, ro[i], e[i].u, so);
-                t.template load<FAST>(sb, ro[i], e[i].v, so + pbytes);
+                t.load(sb, ro[i], e[i].u, so);
+                t.load(sb, ro[i], e[i].v, so + pbytes);
             }
         }
     };
 #pragma unroll
     for (int i = 0; i < RW; ++i) {
-        t.template load<FAST>(il, ro[i + 1], x[i + 1].u);
-        t.template load<FAST>(im, ro[i + 1], x[i + 1].v);
+        t.load(il, ro[i + 1], x[i + 1].u);
+        t.load(im, ro[i + 1], x[i + 1].v);
     }
     fetch(0, ea);
-    if (FAST && t.any_rev) {
+    if (t.any_rev) {
 #pragma unroll
         for (int i = 1; i <= RW; ++i) {
             t.unmirror(x[i].u);
@@ -122,7 +122,7 @@ __device__ __forceinline__ void tile_adjoint_body(const TileAdjArgs &A, int tile
         if (count) {  // cells outside the output may hold anything
 #pragma unroll
             for (int e = 0; e < CPL; ++e)
-                if (FAST || t.cx + e < C) {
+                if (!SPLIT || t.cx + e < C) {
                     const float u = st.u[e], v = st.v[e], l = Cr.u[e], m = Cr.v[e];
                     acc[S_LLU] = __builtin_fmaf(L.u[e], u, acc[S_LLU]);
                     acc[S_LMV] = __builtin_fmaf(L.v[e], v, acc[S_LMV]);
@@ -140,7 +140,7 @@ __device__ __forceinline__ void tile_adjoint_body(const TileAdjArgs &A, int tile
     };
     auto pair = [&](int p, Row<CPL> (&e)[RW + 2], Row<CPL> (&enext)[RW + 2]) __attribute__((always_inline)) {
         fetch(p + 1, enext);
-        if (FAST && t.any_rev) {
+        if (t.any_rev) {
 #pragma unroll
             for (int i = 0; i < RW + 2; ++i) {
                 t.unmirror(e[i].u);
@@ -189,8 +189,8 @@ __device__ __forceinline__ void tile_adjoint_body(const TileAdjArgs &A, int tile
         for (int i = 0; i < RW; ++i) {
             const int r = (half ? rb : ra) + i;
             if (r >= y0 && r < y1) {
-                t.template store<FAST>(ol, ro[i + 1], C, x[i + 1].u);
-                t.template store<FAST>(om, ro[i + 1], C, x[i + 1].v);
+                t.store(ol, ro[i + 1], C, x[i + 1].u);
+                t.store(om, ro[i + 1], C, x[i + 1].v);
             }
         }
     }
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(512) void tile_adjoint_kernel(TileAdjArgs A)
     if (tl >= A.t.ntiles) return;
     const int strip = tl / A.t.nsegs, seg = tl - strip * A.t.nsegs;
     const int x0 = strip * A.t.wout - A.t.kpad, y0 = seg * A.t.h, y1 = min(y0 + A.t.h, A.t.R);
-    if (A.t.vec_ok || (x0 >= 0 && x0 + 32 * CPL <= A.t.C))
+    if (may_split<CPL>(A.t, x0))
         tile_adjoint_body<CPL, RW, true, LAMS>(A, tl, x0, y0, y1, tile_smem);
     else
         tile_adjoint_body<CPL, RW, false, LAMS>(A, tl, x0, y0, y1, tile_smem);

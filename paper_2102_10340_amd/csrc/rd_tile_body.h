@@ -105,16 +105,20 @@ __device__ __forceinline__ void row_update(const typename M::Params &g, const Ro
     D = o;
 }
 
-// Column addressing of one lane.  FAST tiles move a lane's columns with one
-// vector access: inside the grid always (rows need only 4-byte alignment), and
-// at its edges where C % CPL == 0, since a lane's columns then map to one
-// aligned run of columns, reversed (`rev`) where the zero-flux mirror folds them.
-// Other tiles map and move each column on its own.
-template <int CPL>
+// Column addressing of one lane.  A lane moves its CPL columns with one vector
+// access (rows need only 4-byte alignment): also at the grid's edges, where the
+// boundary rule maps a lane's columns onto one run of columns, reversed (`rev`)
+// where the zero-flux mirror folds them.  Only lanes whose columns a fold or a
+// wrap splits (the lane across the right edge where C % CPL != 0, and lanes of
+// grids narrower than a run) move each column on its own; SPLIT tiles may hold
+// such lanes.  Moving every column of an edge tile on its own made 777x1301 run
+// at 1.60 us per step instead of 1.37.
+template <int CPL, bool SPLIT>
 struct HalfTile {
     int cx;                // first column of the lane (boundary-extended)
     bool lane_out;         // the lane's columns are output columns
-    bool rev, any_rev;     // this lane's columns are mirrored; some lane's are
+    bool rev, any_rev;     // this lane's columns are mirrored; some lane's may be
+    bool split;            // SPLIT tiles: this lane's columns are no run
     unsigned vo, mo[CPL];  // byte offsets: of the run, of each mapped column
 
     __device__ __forceinline__ void setup(const TileArgs &A, int x0)
@@ -123,36 +127,45 @@ struct HalfTile {
         cx = x0 + oc;
         const int m0 = map_index(cx, A.C, A.bc), m1 = map_index(cx + CPL - 1, A.C, A.bc);
         rev = m1 < m0;
-        any_rev = A.bc != BC_PERIODIC && (x0 < 0 || x0 + 32 * CPL > A.C);
-        vo = 4u * (unsigned)min(m0, m1);
+        split = false;
+        if (SPLIT) {
+            bool up = true, down = true;
 #pragma unroll
-        for (int e = 0; e < CPL; ++e) mo[e] = 4u * (unsigned)map_index(cx + e, A.C, A.bc);
+            for (int e = 0; e < CPL; ++e) {
+                const int m = map_index(cx + e, A.C, A.bc);
+                up &= m == m0 + e;
+                down &= m == m0 - e;
+                mo[e] = 4u * (unsigned)m;
+            }
+            rev = down;
+            split = !up && !down;
+        }
+        any_rev = SPLIT || (A.bc != BC_PERIODIC && (x0 < 0 || x0 + 32 * CPL > A.C));
+        vo = split ? 0u : 4u * (unsigned)min(m0, m1);
         lane_out = oc >= A.kpad && oc < A.kpad + A.wout && cx < A.C;
     }
 
-    template <bool FAST>
     __device__ __forceinline__ void load(const Buf &b, unsigned ro, float (&x)[CPL],
                                          unsigned soff = 0) const
     {
-        if (FAST) {
-            buf_load<CPL>(b, vo + ro, soff, x);
-        } else {
+        if (SPLIT && split) {
 #pragma unroll
             for (int e = 0; e < CPL; ++e) x[e] = buf_load1(b, mo[e] + ro, soff);
+        } else {
+            buf_load<CPL>(b, vo + ro, soff, x);
         }
     }
 
-    // output columns lie inside the grid, where vo is the lane's own column
-    template <bool FAST>
+    // for output lanes: their columns inside the grid are their own, in order
     __device__ __forceinline__ void store(const Buf &b, unsigned ro, int C, const float (&x)[CPL],
                                           unsigned soff = 0) const
     {
-        if (FAST) {
-            buf_store<CPL>(b, vo + ro, soff, x);
-        } else {
+        if (SPLIT && cx + CPL > C) {
 #pragma unroll
             for (int e = 0; e < CPL; ++e)
                 if (cx + e < C) buf_store1(b, 4u * (unsigned)(cx + e) + ro, soff, x[e]);
+        } else {
+            buf_store<CPL>(b, vo + ro, soff, x);
         }
     }
 
@@ -166,6 +179,16 @@ struct HalfTile {
         }
     }
 };
+
+// Whether a tile whose first column is x0 may hold split lanes: not where C is a
+// multiple of CPL (folds and wraps then fall between runs, as tile columns and
+// kpad are multiples of CPL too), nor left of the right edge with the left halo
+// inside one fold.
+template <int CPL>
+__device__ __forceinline__ bool may_split(const TileArgs &A, int x0)
+{
+    return !A.vec_ok && (x0 + 32 * CPL > A.C || -x0 > A.C);
+}
 
 // The LDS through which a lane's block trades rows with its neighbours:
 // [buffer][layer][block][first, last row][32 lanes] of CPL floats.
@@ -214,7 +237,7 @@ struct BlockLds {
 // LDS bytes of a workgroup: [buffer][layer][block][first, last row][32 lanes].
 constexpr int tile_lds_bytes(int cpl, int w) { return 2 * 2 * (2 * w) * 2 * 32 * 4 * cpl; }
 
-template <class M, int CPL, int RW, bool FAST, bool REC>
+template <class M, int CPL, int RW, bool SPLIT, bool REC>
 __device__ __forceinline__ void tile_body(const TileStepArgsT<M> &A, int x0, int y0, int y1, char *smem)
 {
     const int C = A.t.C, R = A.t.R, bc = A.t.bc, K = A.K;
@@ -225,7 +248,7 @@ __device__ __forceinline__ void tile_body(const TileStepArgsT<M> &A, int x0, int
     const int W = (int)blockDim.y;
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
     const int lane = (int)threadIdx.x, half = lane >> 5;
-    HalfTile<CPL> t;
+    HalfTile<CPL, SPLIT> t;
     t.setup(A.t, x0);
     const int q0 = 2 * w * RW;                     // first tile row of the wavefront
     const int ra = y0 - K + q0, rb = ra + RW;      // first grid row of its two blocks
@@ -240,10 +263,10 @@ __device__ __forceinline__ void tile_body(const TileStepArgsT<M> &A, int x0, int
         const unsigned r0 = row_off(min(ra + i, rlast), R, C, bc);
         const unsigned r1 = row_off(min(rb + i, rlast), R, C, bc);
         const unsigned ro = half ? r1 : r0;
-        t.template load<FAST>(iu, ro, x[i + 1].u);
-        t.template load<FAST>(iv, ro, x[i + 1].v);
+        t.load(iu, ro, x[i + 1].u);
+        t.load(iv, ro, x[i + 1].v);
     }
-    if (FAST && t.any_rev) {
+    if (t.any_rev) {
 #pragma unroll
         for (int i = 1; i <= RW; ++i) {
             t.unmirror(x[i].u);
@@ -298,8 +321,8 @@ __device__ __forceinline__ void tile_body(const TileStepArgsT<M> &A, int x0, int
             const int r = r0 + i;
             if (r >= y0 && r < y1) {
                 const unsigned ro = 4u * (unsigned)r * (unsigned)C;
-                t.template store<FAST>(bu, ro, C, x[i + decltype(slot0)::value].u, soff);
-                t.template store<FAST>(bv, ro, C, x[i + decltype(slot0)::value].v, soff);
+                t.store(bu, ro, C, x[i + decltype(slot0)::value].u, soff);
+                t.store(bv, ro, C, x[i + decltype(slot0)::value].v, soff);
             }
         }
     };
@@ -332,7 +355,7 @@ __global__ __launch_bounds__(1024) void tile_step_kernel(TileStepArgsT<M> A)
     if (tl >= A.t.ntiles) return;
     const int strip = tl / A.t.nsegs, seg = tl - strip * A.t.nsegs;
     const int x0 = strip * A.t.wout - A.t.kpad, y0 = seg * A.t.h, y1 = min(y0 + A.t.h, A.t.R);
-    if (A.t.vec_ok || (x0 >= 0 && x0 + 32 * CPL <= A.t.C))
+    if (may_split<CPL>(A.t, x0))
         tile_body<M, CPL, RW, true, REC>(A, x0, y0, y1, tile_smem);
     else
         tile_body<M, CPL, RW, false, REC>(A, x0, y0, y1, tile_smem);
