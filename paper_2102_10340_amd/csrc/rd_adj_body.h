@@ -508,6 +508,7 @@ __device__ __forceinline__ void batch_tile_args(const BatchAdjArgs &B, int id, A
     A.t.ntiles = 0;
     A.t.per_xcd = 0;
     A.t.vec_ok = (in.C % CPL) == 0;
+    A.t.anchored = 0;
     A.in_l = B.in + in.off;
     A.in_m = A.in_l + (size_t)in.R * in.C;
     A.out_l = B.out + in.off;

@@ -305,6 +305,19 @@ struct Pingpong {
     }
 };
 
+// Columns per lane of plain 8-step passes of grids beyond the resident tiles':
+// four where pairs of wavefronts run them, unless the last strip would be mostly
+// idle; else four from 3072^2 on and two below (us per step, zero-flux, four in
+// pairs / two / one: 2560^2 4.84 / 5.48 / 6.62, 1500x5000 5.33 / 6.16 / 7.33,
+// 12000x600 5.76 / 6.50 / 7.18, 20000x400 6.03 / 7.05 / 8.20; four without pairs /
+// two: 2501x2503 6.25 / 5.45).
+int plain_cols(const rdcnn_sim *h)
+{
+    if (rd::pair_pass(h->bc, h->R, h->C, rd::kPairCpl, rd::kPairDepth) && h->C >= 384)
+        return rd::kPairCpl;
+    return h->R >= 3072 && h->C >= 3072 ? 4 : 2;
+}
+
 // Default pass settings for a grid when the caller has not forced any (from
 // sweeps on MI355X: wide strips and deep passes pay off only on large grids;
 // smaller grids are latency bound and want more, narrower wavefronts).
@@ -333,16 +346,8 @@ void auto_config(const rdcnn_sim *h, int *cpl, int *depth, int *seg_rows, bool r
         if (want < 1) want = 1;
         long long seg = (h->R + want - 1) / want;
         *seg_rows = (int)(seg < 4 ? 4 : seg);
-    } else if (h->R >= 3072 && h->C >= 3072) {
-        *cpl = 4;
-        *depth = 8;
-    } else if (h->R >= 2048 && h->C >= 2048) {
-        // four columns per lane leave too few wavefronts below ~3072^2:
-        // 992 against 802 Gcell-updates/s at 2048^2, 1150 against 1063 at 2560^2
-        *cpl = 2;
-        *depth = 8;
     } else {
-        *cpl = 1;
+        *cpl = plain_cols(h);
         *depth = 8;
     }
 }
@@ -351,9 +356,8 @@ void auto_config(const rdcnn_sim *h, int *cpl, int *depth, int *seg_rows, bool r
 // (the instantiated depths), one step per pass at a zero-flux edge when the
 // update is not mirror-exact for these parameters.
 // Pass shape of a grid of another cell model: the forced settings, else 8
-// steps per pass with 4 columns per lane from 3072^2 (models instantiated
-// that wide), 2 from 2048^2, 1 below; widths beyond the model's widest are
-// narrowed to it.
+// steps per pass with plain_cols columns per lane for Gray-Scott; for the CNN 2
+// from 2048^2, 1 below; widths beyond the model's widest are narrowed to it.
 void model_shape(const rdcnn_sim *h, int *cpl, int *depth, int *seg)
 {
     const int wmax = rd::model_max_cpl(h->model);
@@ -361,7 +365,9 @@ void model_shape(const rdcnn_sim *h, int *cpl, int *depth, int *seg)
     *depth = h->depth;
     *seg = h->seg_rows;
     if (h->kind == 0) {
-        *cpl = h->R >= 3072 && h->C >= 3072 ? 4 : h->R >= 2048 && h->C >= 2048 ? 2 : 1;
+        *cpl = h->model == rd::MODEL_GRAY_SCOTT ? plain_cols(h)
+               : h->R >= 2048 && h->C >= 2048   ? 2
+                                                : 1;
         *depth = 8;
         *seg = 0;
     }
@@ -373,7 +379,7 @@ int run_model_steps(rdcnn_sim *h, long long n)
     if (h->kind == 1) return fail(RDCNN_EINVAL, "rdcnn_step: the one-thread-per-cell kernel "
                                                 "exists for FitzHugh-Nagumo only");
     rd::TilePlan plan;
-    if (h->kind == 0 && h->model == rd::MODEL_GRAY_SCOTT && rd::tile_plan(h->R, h->C, n, &plan)) {
+    if (h->kind == 0 && h->model == rd::MODEL_GRAY_SCOTT && rd::tile_plan(h->R, h->C, h->bc, n, &plan)) {
         for (long long i = 0; i < plan.passes; ++i) {
             const hipError_t e = rd::launch_tile_gs(h->buf[h->cur], h->buf[1 - h->cur], h->R, h->C,
                                                     h->bc, h->mparams, plan.at(i), h->stream);
@@ -389,7 +395,9 @@ int run_model_steps(rdcnn_sim *h, long long n)
         int k = 8;
         while (k > 1 && (k > depth || k > n)) k >>= 1;
         rd::StreamGeom geom;
-        if (!rd::stream_geometry(h->R, h->C, cpl, k, seg, &geom))
+        if (!(h->model == rd::MODEL_GRAY_SCOTT
+                  ? rd::plain_geometry(h->R, h->C, h->bc, cpl, k, seg, &geom)
+                  : rd::stream_geometry(h->R, h->C, cpl, k, seg, &geom)))
             return fail(RDCNN_EINVAL, "rdcnn_step: cannot tile %dx%d with cpl=%d depth=%d", h->R,
                         h->C, cpl, k);
         hipError_t e = rd::launch_model(h->model, h->buf[h->cur], h->buf[1 - h->cur], h->R, h->C,
@@ -476,7 +484,7 @@ int run_steps(rdcnn_sim *h, long long n, float *rec, bool rec_even = false, int 
     int kind = h->kind, cpl = h->cpl, depth = h->depth, seg = h->seg_rows;
     if (kind == 0 && !rec) {
         rd::TilePlan plan;
-        if (rd::tile_plan(h->R, h->C, n, &plan)) {
+        if (rd::tile_plan(h->R, h->C, h->bc, n, &plan)) {
             for (long long i = 0; i < plan.passes; ++i) {
                 const hipError_t e = rd::launch_tile(h->buf[h->cur], h->buf[1 - h->cur], h->R, h->C,
                                                      h->bc, h->g, plan.at(i), h->stream);
@@ -542,7 +550,8 @@ int run_steps(rdcnn_sim *h, long long n, float *rec, bool rec_even = false, int 
         } else {
             const int k = (int)(n < depth ? n : depth);
             rd::StreamGeom geom;
-            if (!rd::stream_geometry(h->R, h->C, cpl, k, seg, &geom))
+            if (!(rec ? rd::stream_geometry(h->R, h->C, cpl, k, seg, &geom)
+                      : rd::plain_geometry(h->R, h->C, h->bc, cpl, k, seg, &geom)))
                 return fail(RDCNN_EINVAL, "rdcnn_step: cannot tile %dx%d with cpl=%d depth=%d",
                             h->R, h->C, cpl, k);
             if (rec && rec_even && q % 2 == 1)  // depth-1 passes: odd times are not kept
@@ -1095,7 +1104,7 @@ int rdcnn_step_checkpoints(rdcnn_t h, long long T, long long S, float *ckpt_dev)
         long long k = kind == 1 ? 1 : depth;
         if (q % S == 0 && tiles) {
             pass = 0;
-            if (bound - q != plan_len) tiles = rd::tile_plan(h->R, h->C, bound - q, &plan);
+            if (bound - q != plan_len) tiles = rd::tile_plan(h->R, h->C, h->bc, bound - q, &plan);
             plan_len = bound - q;
         }
         if (tiles) k = plan.at(pass).K;
@@ -1110,7 +1119,7 @@ int rdcnn_step_checkpoints(rdcnn_t h, long long T, long long S, float *ckpt_dev)
             e = rd::launch_naive(in, out, h->R, h->C, h->bc, h->g, h->stream);
         } else {
             rd::StreamGeom geom;
-            if (!rd::stream_geometry(h->R, h->C, cpl, (int)k, seg, &geom))
+            if (!rd::plain_geometry(h->R, h->C, h->bc, cpl, (int)k, seg, &geom))
                 return fail(RDCNN_EINVAL, "%s: cannot tile %dx%d with cpl=%d depth=%lld", who, h->R,
                             h->C, cpl, k);
             e = rd::launch_stream(in, out, h->R, h->C, h->bc, h->g, geom, h->stream);
@@ -1376,7 +1385,7 @@ int rdcnn_pass_config(rdcnn_t h, int *kind, int *depth, int *cols_per_lane, int 
         return fail(RDCNN_EINVAL, "rdcnn_pass_config: NULL argument");
     int k = h->kind == 3 ? 2 : h->kind, cpl = h->cpl, d = h->depth, seg = h->seg_rows;
     rd::TilePlan plan;
-    if (h->kind == 0 && h->model != rd::MODEL_CNN && rd::tile_plan(h->R, h->C, 1 << 20, &plan)) {
+    if (h->kind == 0 && h->model != rd::MODEL_CNN && rd::tile_plan(h->R, h->C, h->bc, 1 << 20, &plan)) {
         *kind = 4;
         *depth = plan.base.K;
         *cols_per_lane = plan.base.cpl;
@@ -1395,9 +1404,11 @@ int rdcnn_pass_config(rdcnn_t h, int *kind, int *depth, int *cols_per_lane, int 
         seg = 1;
     } else {
         rd::StreamGeom geom;
-        if (!rd::stream_geometry(h->R, h->C, cpl, d, seg, &geom))
+        if (!(h->model == rd::MODEL_CNN
+                  ? rd::stream_geometry(h->R, h->C, cpl, d, seg, &geom)
+                  : rd::plain_geometry(h->R, h->C, h->bc, cpl, d, seg, &geom)))
             return fail(RDCNN_EINVAL, "rdcnn_pass_config: cannot tile %dx%d", h->R, h->C);
-        seg = geom.h;
+        seg = geom.paired ? (geom.h + 1) / 2 : geom.h;
     }
     *kind = k;
     *depth = d;

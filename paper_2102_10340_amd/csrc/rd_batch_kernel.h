@@ -43,6 +43,7 @@ __global__ __launch_bounds__(64) void batch_step_kernel(BatchArgs B)
     A.t.ntiles = 0;
     A.t.per_xcd = 0;
     A.t.vec_ok = (in.C % CPL) == 0;
+    A.t.anchored = 0;
     A.in = B.in + in.off;
     A.out = B.out + in.off;
     A.g = in.g;

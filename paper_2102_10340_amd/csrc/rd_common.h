@@ -79,6 +79,14 @@ __device__ __forceinline__ float from_right_lane(float x)
                                                                  0x130, 0xF, 0xF, true));
 }
 
+// Barrier that orders LDS accesses only (global stores stay in flight).
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Workgroups are handed to the 8 XCDs round-robin; renumber them so that each
 // XCD gets a contiguous run of tiles (neighbouring tiles share halo lines in
 // that XCD's L2).

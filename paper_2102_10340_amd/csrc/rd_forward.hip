@@ -18,7 +18,9 @@
 //                       valid region shrinks by one cell per level), read from
 //                       the boundary-extended grid (map_index), so the boundary
 //                       rule costs nothing inside the loop.  Its template
-//                       instances are compiled in rd_fwd_r*.hip.
+//                       instances are compiled in rd_fwd_r*.hip; plain passes of
+//                       8 steps, four columns per lane, go to pairs of
+//                       wavefronts (rd_pair.h) where their conditions hold.
 #include "rd_fwd_kernel.h"
 
 namespace rd {
@@ -189,23 +191,18 @@ hipError_t launch_naive(const float *in, float *out, int R, int C, int bc, const
 
 // ---------------------------------------------------------------- streamed
 
-bool stream_geometry(int R, int C, int cpl, int depth, int seg_rows, StreamGeom *g)
+namespace {
+
+// The tiling from its strips: segments of h rows, h = 0 for about two resident
+// wavefronts per SIMD (1024 SIMDs), `waves` wavefronts a tile.
+bool cut_segments(int R, int h, int waves, StreamGeom *g)
 {
-    if (cpl != 1 && cpl != 2 && cpl != 4) return false;
-    if (depth < 1 || depth > max_depth(cpl)) return false;
-    g->cpl = cpl;
-    g->depth = depth;
-    g->kpad = (depth + cpl - 1) / cpl * cpl;
-    g->wout = 64 * cpl - 2 * g->kpad;
-    if (g->wout <= 0) return false;
-    g->nstrips = (C + g->wout - 1) / g->wout;
-    int h = seg_rows;
     if (h <= 0) {
-        // Aim at about two resident wavefronts per SIMD (1024 SIMDs).
-        long long want = 2048 / g->nstrips;
+        long long want = 2048 / waves / g->nstrips;
         if (want < 1) want = 1;
         h = (int)(((long long)R + want - 1) / want);
-        if (h < 4) h = 4;
+        h = (h + waves - 1) / waves * waves;
+        if (h < 4 * waves) h = 4 * waves;
     }
     if (h > R) h = R;
     g->h = h;
@@ -215,6 +212,32 @@ bool stream_geometry(int R, int C, int cpl, int depth, int seg_rows, StreamGeom 
     g->ntiles = (int)nt;
     g->per_xcd = (g->ntiles + 7) / 8;
     return true;
+}
+
+}  // namespace
+
+bool stream_geometry(int R, int C, int cpl, int depth, int seg_rows, StreamGeom *g)
+{
+    if (cpl != 1 && cpl != 2 && cpl != 4) return false;
+    if (depth < 1 || depth > max_depth(cpl)) return false;
+    g->cpl = cpl;
+    g->depth = depth;
+    g->kpad = (depth + cpl - 1) / cpl * cpl;
+    g->wout = 64 * cpl - 2 * g->kpad;
+    if (g->wout <= 0) return false;
+    g->paired = g->anchored = false;
+    g->nstrips = (C + g->wout - 1) / g->wout;
+    return cut_segments(R, seg_rows, 1, g);
+}
+
+bool plain_geometry(int R, int C, int bc, int cpl, int depth, int seg_rows, StreamGeom *g)
+{
+    if (!stream_geometry(R, C, cpl, depth, seg_rows, g)) return false;
+    g->paired = pair_pass(bc, R, C, cpl, depth);
+    if (!g->paired) return true;
+    g->anchored = strips_anchored(bc, R, C, cpl, depth);
+    if (g->anchored) g->nstrips = C > 64 * cpl ? (C - 2 * g->kpad + g->wout - 1) / g->wout : 1;
+    return cut_segments(R, seg_rows > R / 2 ? R : 2 * seg_rows, 2, g);
 }
 
 namespace {
@@ -249,6 +272,7 @@ TileArgs tile_args(int R, int C, int bc, const StreamGeom &geom)
     t.ntiles = geom.ntiles;
     t.per_xcd = geom.per_xcd;
     t.vec_ok = (C % geom.cpl) == 0;
+    t.anchored = geom.anchored;
     return t;
 }
 
@@ -257,7 +281,9 @@ hipError_t launch_stream(const float *in, float *out, int R, int C, int bc, cons
                          bool rec_even, bool skip_level0, int rec_every)
 {
     if (rec_every < 1) return hipErrorInvalidValue;
-    StreamFn f = pick_stream(!rec ? 0 : !rec_even ? 1 : skip_level0 ? 3 : 2, geom.cpl, geom.depth);
+    StreamFn f = geom.paired ? (rec ? nullptr : pair_fn())
+                             : pick_stream(!rec ? 0 : !rec_even ? 1 : skip_level0 ? 3 : 2, geom.cpl,
+                                           geom.depth);
     if (!f) return hipErrorInvalidValue;
     StreamArgs a;
     a.t = tile_args(R, C, bc, geom);
@@ -266,7 +292,7 @@ hipError_t launch_stream(const float *in, float *out, int R, int C, int bc, cons
     a.g = g;
     a.rec = rec ? rec + rec_q0 * rec_every * 2LL * R * C : nullptr;
     a.rec_stride = 8u * (unsigned)rec_every * (unsigned)R * (unsigned)C;
-    hipLaunchKernelGGL(f, dim3((unsigned)(8 * geom.per_xcd)), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(f, dim3((unsigned)(8 * geom.per_xcd)), dim3(64, geom.paired ? 2 : 1), 0, s, a);
     return hipGetLastError();
 }
 

@@ -61,4 +61,8 @@ StreamFn stream_fn_r2c2(int depth);
 StreamFn stream_fn_r3c1(int depth);
 StreamFn stream_fn_r3c2(int depth);
 
+// Plain passes by pairs of wavefronts (rd_pair.h): kPairDepth steps, kPairCpl
+// columns per lane.
+StreamFn pair_fn();
+
 }  // namespace rd

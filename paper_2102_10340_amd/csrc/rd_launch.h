@@ -47,11 +47,24 @@ struct StreamGeom {
     int wout;    // output columns of a strip (64*cpl - 2*kpad)
     int h;       // output rows of a segment
     int nstrips, nsegs, ntiles, per_xcd;
+    bool paired, anchored;  // a pass by pairs of wavefronts; strips_anchored
 };
 
 // Fill in the strip/segment decomposition; seg_rows <= 0 picks a default.
 // Returns false if the shape cannot be tiled with these settings.
 bool stream_geometry(int R, int C, int cpl, int depth, int seg_rows, StreamGeom *g);
+
+// Whether pairs of wavefronts run a plain pass of a model of four neighbours
+// (rd_pair.h): where they have an instance and every lane's columns are a vector.
+constexpr int kPairCpl = 4, kPairDepth = 8;
+inline bool pair_pass(int bc, int R, int C, int cpl, int depth)
+{
+    return cpl == kPairCpl && depth == kPairDepth && C % cpl == 0 && R > depth + kFetchPast &&
+           (bc == BC_PERIODIC || strips_anchored(bc, R, C, cpl, depth));
+}
+// The tiling of a plain pass of such a model.  seg_rows are the rows of a
+// wavefront, so a pair's tile has twice as many.
+bool plain_geometry(int R, int C, int bc, int cpl, int depth, int seg_rows, StreamGeom *g);
 
 // Kernel arguments describing the tiling of `geom`.
 TileArgs tile_args(int R, int C, int bc, const StreamGeom &geom);
@@ -85,9 +98,13 @@ struct TileShape {
     int cpl, rw, w, K;
 };
 constexpr int kMaxTileDepth = 16;
-// Largest grid that takes them.  us per step, resident tiles against the best
-// streamed shape: 2048^2 3.3 / 4.3, 2304^2 4.51 / 5.11, 2400^2 5.22 / 5.62.
+// Largest grids that take them.  us per step, resident tiles against pairs of
+// wavefronts on a zero-flux grid: 2048^2 3.33 / 4.07, 2304^2 4.50 / 4.62, 2400^2
+// 4.53 / 4.67 (the pairs reach 4.84 at 2560^2); on a torus, whose strips all take
+// the pairs' short path: 3600x1200 3.54 / 3.49, 2048^2 3.35 / 3.75, 2200^2 4.34 /
+// 3.91, 2400^2 4.59 / 4.30.
 constexpr long long kMaxTileCells = 6000000;
+constexpr long long kMaxTileCellsTorus = 4500000;  // where pairs are the other choice
 inline int tile_out_rows(const TileShape &s) { return 2 * s.w * s.rw - 2 * s.K; }
 
 // T steps as `passes` passes: the first `deeper` of shape `deep`, the others of
@@ -99,7 +116,7 @@ struct TilePlan {
 };
 // The fastest plan by the launcher's cost model; false if the grid is for the
 // streamed kernel.
-bool tile_plan(int R, int C, long long T, TilePlan *plan);
+bool tile_plan(int R, int C, int bc, long long T, TilePlan *plan);
 // Recording passes: the (even) depth of the passes of an n-step run, 0 if the
 // grid is for the streamed kernel; the shape of a pass of K steps.
 int tile_record_depth(int R, int C, long long n);

@@ -6,6 +6,7 @@
 
 #include "rd_fwd_body.h"
 #include "rd_launch.h"
+#include "rd_pair.h"
 
 namespace rd {
 
@@ -75,7 +76,11 @@ template <class M>
 hipError_t launch_as(const float *in, float *out, int R, int C, int bc,
                      const typename M::Params &p, const StreamGeom &geom, hipStream_t s)
 {
-    ModelFn<M> f = pick_model<M>(geom.cpl, geom.depth);
+    ModelFn<M> f = nullptr;
+    if constexpr (!M::kDiag) {
+        if (geom.paired) f = &pair_step_kernel<M, kPairCpl, kPairDepth>;
+    }
+    if (!geom.paired) f = pick_model<M>(geom.cpl, geom.depth);
     if (!f) return hipErrorInvalidValue;
     StreamArgsT<M> a;
     a.t = tile_args(R, C, bc, geom);
@@ -84,7 +89,8 @@ hipError_t launch_as(const float *in, float *out, int R, int C, int bc,
     a.g = p;
     a.rec = nullptr;
     a.rec_stride = 0;
-    hipLaunchKernelGGL(f, dim3((unsigned)(8 * geom.per_xcd)), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(f, dim3((unsigned)(8 * geom.per_xcd)), dim3(64, geom.paired ? 2 : 1), 0,
+                       s, a);
     return hipGetLastError();
 }
 

@@ -107,8 +107,29 @@ __device__ __forceinline__ void buf_store1(const Buf &b, unsigned voff, unsigned
 struct TileArgs {
     int R, C, bc;
     int wout, kpad, h, nsegs, ntiles, per_xcd;
-    int vec_ok;  // C % CPL == 0: rows of a plane keep CPL-float alignment
+    int vec_ok;    // C % CPL == 0: rows of a plane keep CPL-float alignment
+    int anchored;  // strips end at the grid's zero-flux sides (strips_anchored)
 };
+
+// A walk over rows rbase .. rbase+n_real-1 fetches up to this many rows past
+// its last one (row prefetches of the last iterations; nothing uses them).  A
+// tile takes the unmapped-row (ROWS_IN) path only if those rows are inside the
+// grid too: the row offset travels in a buffer instruction's scalar offset, so
+// every row it names must lie inside the plane.
+constexpr int kFetchPast = 3;
+
+// Whether the strips of a paired pass (rd_pair.h) of K steps end at the grid's
+// sides: at a zero-flux side the outermost lane is its own neighbour (which gives
+// the bits of a mirrored halo, the update adding west and east), so the side
+// strips carry no halo there and every lane loads a vector of the grid.  4096
+// columns take 17 strips of 64x4 that way instead of 18, and the halo strips'
+// loads, four to a vector, made them the last of their launch: 88.3 us a pass
+// against 83.3.  Needs whole vectors, a grid of at least one strip and rows that
+// one reflection maps.
+inline bool strips_anchored(int bc, int R, int C, int cpl, int K)
+{
+    return bc == BC_ZEROFLUX && C % cpl == 0 && C >= 64 * cpl && R > K + kFetchPast;
+}
 
 // Where one wavefront's tile sits, and which of its lanes own output columns.
 template <int CPL>
@@ -117,7 +138,8 @@ struct Tile {
     int x0;              // first extended column of the strip
     int y0, y1;          // output rows [y0, y1)
     int cx;              // first column of this lane
-    bool fast;           // whole strip inside the grid and C % CPL == 0: vector I/O
+    bool fast;           // every lane's columns are a vector of one row: vector I/O
+    bool edge;           // an outermost lane is at a zero-flux side (anchored strips)
     bool lane_out;       // this lane's columns are output columns of the tile
     unsigned vo;         // byte offset of the lane's first column (fast tiles)
     unsigned mo[CPL];    // byte offset of each boundary-mapped column (edge tiles)
@@ -130,7 +152,9 @@ struct Tile {
         const int strip = tl / A.nsegs;
         const int seg = tl - strip * A.nsegs;
         const int sy0 = seg * A.h;
-        setup(A, tl, strip * A.wout - A.kpad, sy0, min(sy0 + A.h, A.R));
+        setup(A, tl,
+              A.anchored ? min(strip * A.wout, A.C - 64 * CPL) : strip * A.wout - A.kpad, sy0,
+              min(sy0 + A.h, A.R));
         return true;
     }
 
@@ -142,12 +166,20 @@ struct Tile {
         y0 = ry0;
         y1 = ry1;
         cx = x0 + CPL * (int)threadIdx.x;
-        fast = A.vec_ok && x0 >= 0 && x0 + 64 * CPL <= A.C;
-        vo = 4u * (unsigned)(cx < 0 ? 0 : cx);
+        // a strip inside the grid, or a torus of whole vectors, where a lane's columns
+        // stay together as they wrap (a buffer access needs 4-byte alignment only)
+        fast = (x0 >= 0 && x0 + 64 * CPL <= A.C) || (A.vec_ok && A.bc == BC_PERIODIC);
+        edge = A.anchored && (x0 == 0 || x0 + 64 * CPL == A.C);
 #pragma unroll
         for (int e = 0; e < CPL; ++e) mo[e] = 4u * (unsigned)map_index(cx + e, A.C, A.bc);
-        const int oc = cx - x0;
-        lane_out = oc >= A.kpad && oc < A.kpad + A.wout && cx < A.C;
+        vo = mo[0];
+        int lo = x0 + A.kpad, hi = lo + A.wout;
+        if (A.anchored) {
+            // the last strip starts early: its output follows the strip before
+            lo = x0 == 0 ? 0 : (x0 + A.wout - 1) / A.wout * A.wout + A.kpad;
+            if (x0 + 64 * CPL == A.C) hi = A.C;
+        }
+        lane_out = cx >= lo && cx < hi && cx < A.C;
     }
 
     // 1 if element e of this lane holds an output cell of the tile, else 0.
@@ -191,12 +223,14 @@ __device__ __forceinline__ unsigned row_off(int r, int R, int C, int bc)
     return 4u * (unsigned)map_index(r, R, bc) * (unsigned)C;
 }
 
-// A walk over rows rbase .. rbase+n_real-1 fetches up to this many rows past
-// its last one (row prefetches of the last iterations; nothing uses them).  A
-// tile takes the unmapped-row (ROWS_IN) path only if those rows are inside the
-// grid too: the row offset travels in a buffer instruction's scalar offset, so
-// every row it names must lie inside the plane.
-constexpr int kFetchPast = 3;
+// The same for a row at most R outside the grid, without loops or branches.
+__device__ __forceinline__ unsigned row_off_near(int r, int R, int C, int bc)
+{
+    const int lo = bc == BC_PERIODIC ? r + R : -1 - r;
+    r = r < 0 ? lo : r;
+    const int hi = bc == BC_PERIODIC ? r - R : 2 * R - 1 - r;
+    return 4u * (unsigned)(r >= R ? hi : r) * (unsigned)C;
+}
 
 // Slots of the three-row window of time level j while row `it` of level 0 is
 // read: row it-j (newest), it-j-1 (centre) and it-j-2 (oldest) of level j sit

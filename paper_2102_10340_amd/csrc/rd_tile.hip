@@ -139,12 +139,14 @@ int even_depth(const Table &tb, long long S)
 
 }  // namespace
 
-bool tile_plan(int R, int C, long long T, TilePlan *plan)
+bool tile_plan(int R, int C, int bc, long long T, TilePlan *plan)
 {
     // Up to here the resident tiles are the faster kind; above, the streamed
     // kernel's wider strips waste less on halos and hide their memory traffic
     // behind the arithmetic.
-    if ((long long)R * C > kMaxTileCells || T < 1) return false;
+    const bool torus_pairs = bc == BC_PERIODIC && pair_pass(bc, R, C, kPairCpl, kPairDepth);
+    const long long most = torus_pairs ? kMaxTileCellsTorus : kMaxTileCells;
+    if ((long long)R * C > most || T < 1) return false;
     const Table &tb = table(R, C, false);
     double best = INFINITY;
     for (int K = 1; K <= kMaxTileDepth; ++K) {
@@ -202,6 +204,7 @@ bool tile_geometry(int R, int C, int bc, const TileShape &sh, TileArgs *t)
     t->ntiles = (int)nt;
     t->per_xcd = (t->ntiles + 7) / 8;
     t->vec_ok = C % sh.cpl == 0;
+    t->anchored = 0;
     return true;
 }
 

@@ -45,14 +45,6 @@ struct TileStepArgsT {
     int rec_first;
 };
 
-// Barrier that orders LDS accesses only (global stores stay in flight).
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Lane i of each 32-lane half receives lane i-1's (i+1's) value of its half,
 // rotating (ds_swizzle rotate mode: bit 10 the direction, bits 9:5 the count).
 __device__ __forceinline__ float half_from_left(float x)
