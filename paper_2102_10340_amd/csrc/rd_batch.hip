@@ -14,7 +14,10 @@
 #include <math.h>
 
 #include <algorithm>
+#include <initializer_list>
+#include <map>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "rd_batch_kernel.h"
@@ -173,7 +176,7 @@ hipError_t launch_batch(const BatchTile *tiles, const BatchInst *insts, int ntil
 // ---------------------------------------------------------------- C ABI
 
 struct TileTable {
-    int depth = 0;
+    int depth = 0, cpl = 0, seg = 0;
     int ntiles = 0;
     rd::BatchTile *dev = nullptr;
 };
@@ -195,6 +198,7 @@ struct rdcnn_batch {
     int cur;
     hipStream_t stream;
     int cpl, depth, seg_rows;  // forced settings, 0 = automatic
+    int auto_cpl, auto_depth, auto_seg;  // the automatic ones, 0 = not yet chosen
     rd::BatchInst *insts_dev;
     std::vector<TileTable> tables;
     int use_graph;
@@ -209,7 +213,7 @@ struct rdcnn_batch {
     int stat_nchunks;
     long long total;                 // floats in one packed state buffer
     std::vector<TileTable> rec_tables;  // recording passes (every instance streamed)
-    int rec_cpl;
+    int rec_cut[2][2];          // automatic cut of full and even-time recording: columns, rows
     // reverse pass: one tile list (cut for adj_depth), per-instance tile lists
     TileTable adj_table;
     int adj_cpl, adj_depth, adj_seg;
@@ -298,6 +302,7 @@ void free_lds(rdcnn_batch *b)
     b->whole_dev = nullptr;
     for (int q = 0; q < 2; ++q) b->whole_count[q] = b->whole_waves[q] = 0;
     b->in_lds.assign(b->n, 0);
+    b->auto_cpl = b->auto_depth = b->auto_seg = 0;
 }
 
 // Decide which instances run whole in one workgroup (in its registers where
@@ -354,11 +359,110 @@ int setup_lds(rdcnn_batch *b)
     return RDCNN_OK;
 }
 
-void batch_config(const rdcnn_batch *b, int *cpl, int *depth, int *seg)
+// What a streamed pass over a tile list costs a wavefront: vector instructions
+// per cell and level, cycles per instruction of a walk alone (one and two columns
+// per lane) and of a SIMD with several.
+struct CutCost {
+    double ops, walk[2], simd;
+};
+constexpr CutCost kStepCost{17.0, {7.6, 5.5}, 3.9}, kAdjCost{39.0, {7.5, 7.5}, 3.85};
+constexpr int kCutDepth = 8;  // steps of a pass the rule below is for
+
+// The batch's sizes with their counts (without the instances held whole, if
+// skip_lds).
+std::map<std::pair<int, int>, int> size_classes(const rdcnn_batch *b, bool skip_lds)
 {
-    *cpl = b->cpl ? b->cpl : 2;
-    *depth = b->depth ? b->depth : 12;
-    *seg = b->seg_rows ? b->seg_rows : 128;
+    std::map<std::pair<int, int>, int> n;
+    for (int i = 0; i < b->n; ++i)
+        if (!(skip_lds && b->in_lds[i])) ++n[{b->R[i], b->C[i]}];
+    return n;
+}
+
+// Tiles of kTallRows rows that K-step passes cut the sizes into.
+constexpr int kTallRows = 128;
+long long tall_tiles(const std::map<std::pair<int, int>, int> &sizes, int cpl, int K)
+{
+    const int wout = 64 * cpl - 2 * ((K + cpl - 1) / cpl * cpl);
+    long long n = 0;
+    for (const auto &z : sizes)
+        n += (long long)z.second * ((z.first.first + kTallRows - 1) / kTallRows) *
+             ((z.first.second + wout - 1) / wout);
+    return n;
+}
+
+// Estimated us of a kCutDepth-step pass with `seg` rows per tile: the fullest
+// SIMD's tiles or the longest walk, whichever is longer.  Short tiles fill the
+// chip and walk quickly, long ones have fewer halo rows.  Within 10 % (rms) of
+// the passes over eight batches of 0.5 to 33 million cells, 10 heights each; the
+// height it picks against 128 rows, us per step: 8 x 256^2 2.02 / 13.0, 40 x
+// 256^2 3.94 / 13.0, 4 x 1024^2 5.14 / 13.4, 16 of 256^2 to 1024^2 6.84 / 14.1;
+// reverse passes, us per step: 8 x 256^2 4.69 / 16.2, 4 x 1024^2 14.2 / 21.2, 10 of
+// 300x417 and 777x333 8.44 / 20.2.
+double cut_us(const std::map<std::pair<int, int>, int> &sizes, int cpl, int seg, const CutCost &c)
+{
+    constexpr int K = kCutDepth, kSimds = 1024;
+    constexpr double kMHz = 2100.0, kFixed = 5.0;
+    const int kpad = (K + cpl - 1) / cpl * cpl, wout = 64 * cpl - 2 * kpad;
+    const double row = c.ops * K * cpl;
+    double sum = 0.0, most = 0.0;
+    int walk = 0;
+    for (const auto &z : sizes) {
+        const int R = z.first.first, strips = (z.first.second + wout - 1) / wout;
+        const int h = seg < R ? seg : R, rest = R % h;
+        const double full = (double)(R / h) * (h + K) + (rest ? rest + K : 0);
+        sum += (double)z.second * strips * full * row;
+        if ((h + K) * row > most) most = (h + K) * row;
+        if (h + 2 * K > walk) walk = h + 2 * K;
+    }
+    if (most == 0.0) return 0.0;
+    const double simd = ceil(sum / (kSimds * most) - 0.02) * most * c.simd;
+    const double alone = walk * row * c.walk[cpl - 1];
+    return kFixed + (simd > alone ? simd : alone) / kMHz;
+}
+
+// The best (columns per lane, rows per tile) among `segs`, cpl from first_cpl on.
+void best_cut(const std::map<std::pair<int, int>, int> &sizes, const CutCost &c, int first_cpl,
+              int last_cpl, std::initializer_list<int> segs, int *cpl, int *seg)
+{
+    double best = INFINITY;
+    for (int w = last_cpl; w >= first_cpl; --w)  // of two that tie, the wider
+        for (int s : segs) {
+            const double us = cut_us(sizes, w, s, c);
+            if (us < best) {
+                best = us;
+                *cpl = w;
+                *seg = s;
+            }
+        }
+}
+
+// Pass shape of plain steps: forced settings; else, of a batch that fills the chip
+// half again with tall tiles, the shape of the least work (12 steps, 128 rows: 64 x
+// 1024^2 40.5 us per step against 43.7 with the cheapest cut's; 72 of 256^2 to
+// 1024^2 25.9 against 23.3 alone, but three such batches on three streams 2475 us
+// against 2660); else the cheapest cut.
+void batch_config(rdcnn_batch *b, int *cpl, int *depth, int *seg)
+{
+    if (b->depth) {
+        *cpl = b->cpl;
+        *depth = b->depth;
+        *seg = b->seg_rows ? b->seg_rows : 128;
+        return;
+    }
+    if (!b->auto_seg) {
+        const auto sizes = size_classes(b, true);
+        b->auto_cpl = 2;
+        b->auto_depth = 12;
+        b->auto_seg = kTallRows;
+        if (tall_tiles(sizes, 2, 12) < 1536) {
+            b->auto_depth = kCutDepth;
+            best_cut(sizes, kStepCost, 1, 2, {8, 12, 16, 24, 32, 48, 64, 96, 128}, &b->auto_cpl,
+                     &b->auto_seg);
+        }
+    }
+    *cpl = b->auto_cpl;
+    *depth = b->auto_depth;
+    *seg = b->auto_seg;
 }
 
 // Tile list for one pass depth: every instance (but those run in LDS, if
@@ -412,12 +516,12 @@ int upload_tiles(const std::vector<rd::BatchTile> &tiles, int depth, TileTable &
     return RDCNN_OK;
 }
 
-// The table of `depth` in a set (built on first use).
+// The table of a pass shape in a set (built on first use).
 int table_in(rdcnn_batch *b, std::vector<TileTable> &set, int cpl, int depth, int seg,
              bool skip_lds, const TileTable **out, bool class_seg = false)
 {
     for (const TileTable &t : set)
-        if (t.depth == depth) {
+        if (t.depth == depth && t.cpl == cpl && t.seg == seg) {
             *out = &t;
             return RDCNN_OK;
         }
@@ -427,6 +531,8 @@ int table_in(rdcnn_batch *b, std::vector<TileTable> &set, int cpl, int depth, in
     TileTable t;
     rc = upload_tiles(tiles, depth, t);
     if (rc != RDCNN_OK) return rc;
+    t.cpl = cpl;
+    t.seg = seg;
     set.push_back(t);
     *out = &set.back();
     return RDCNN_OK;
@@ -479,7 +585,16 @@ int setup_adj(rdcnn_batch *b)
 {
     free_adj(b);
     std::vector<rd::BatchTile> tiles;
-    int rc = build_tiles(b, b->adj_cpl, b->adj_depth, b->adj_seg, false, tiles);
+    int cpl = b->adj_cpl, seg = b->adj_seg;
+    if (!seg) {
+        // two tall tiles a SIMD are enough (72 of 256^2 to 1024^2: 60.6 us per step
+        // with them, 65.2 with the cheapest cut's 64 rows)
+        const auto sizes = size_classes(b, false);
+        seg = kTallRows;
+        if (tall_tiles(sizes, cpl, b->adj_depth) < 2048)
+            best_cut(sizes, kAdjCost, cpl, cpl, {16, 32, 64, 128}, &cpl, &seg);
+    }
+    int rc = build_tiles(b, cpl, b->adj_depth, seg, false, tiles);
     if (rc != RDCNN_OK) return rc;
     std::vector<int> first(b->n + 1, 0), tiles_of(tiles.size());
     for (const rd::BatchTile &t : tiles) ++first[t.inst + 1];
@@ -636,6 +751,7 @@ int rdcnn_batch_create(rdcnn_batch_t *out, int n, const int *rows, const int *co
     b->cur = 0;
     b->stream = (hipStream_t)stream;
     b->cpl = b->depth = b->seg_rows = 0;
+    b->auto_cpl = b->auto_depth = b->auto_seg = 0;
     b->insts_dev = nullptr;
     b->use_graph = 0;
     b->graph = nullptr;
@@ -646,12 +762,12 @@ int rdcnn_batch_create(rdcnn_batch_t *out, int n, const int *rows, const int *co
     b->stat_partial = nullptr;
     b->stat_nchunks = 0;
     b->total = buf_floats;
-    b->rec_cpl = 2;
+    b->rec_cut[0][0] = b->rec_cut[1][0] = 0;
     b->adj_table = TileTable();
-    // reverse-pass defaults from a sweep of 64 x 1024^2 on MI355X
+    // reverse-pass defaults from a sweep of 64 x 1024^2 on MI355X; rows by size
     b->adj_cpl = 1;
-    b->adj_depth = 8;
-    b->adj_seg = 128;
+    b->adj_depth = kCutDepth;
+    b->adj_seg = 0;
     b->adj_first = b->adj_tiles_of = nullptr;
     b->adj_partial = nullptr;
     b->shared_grad = 0;
@@ -733,10 +849,21 @@ int batch_record(rdcnn_batch *b, long long T, float *traj, bool even, const char
     batch_config(b, &cpl, &depth, &seg);
     if (cpl > 2) cpl = 2;  // recording passes exist for 1 or 2 columns per lane
     if (depth > 8) depth = 8;
-    // Recording waits on its stores more than on arithmetic: shorter tiles
-    // led sweeps on 64 x 1024^2 (full: 64 rows; even-time: 32 rows, 0.57
-    // Tcell-steps/s against 0.50 at 64).
-    if (!b->seg_rows) seg = even ? 32 : 64;
+    // Recording waits on its stores more than on arithmetic: shorter tiles than a
+    // plain pass's led sweeps on 64 x 1024^2 (full: 64 rows; even-time: 32 rows,
+    // 0.57 Tcell-steps/s against 0.50 at 64); smaller batches take less where
+    // that fills the chip (6 of 500 x 640, even-time: 31 us a pass against 40).
+    if (!b->depth) {
+        int *cut = b->rec_cut[even ? 1 : 0];
+        if (!cut[0] && even)
+            best_cut(size_classes(b, false), kStepCost, 1, 2, {8, 16, 32}, &cut[0], &cut[1]);
+        else if (!cut[0])
+            best_cut(size_classes(b, false), kStepCost, 1, 2, {8, 16, 32, 64}, &cut[0], &cut[1]);
+        cpl = cut[0];
+        seg = cut[1];
+    } else if (!b->seg_rows) {
+        seg = even ? 32 : 64;
+    }
     if (even) {
         // a pass spans depth/2 recorded states; every pass but the last starts
         // at an even time, so the depth is even
@@ -747,12 +874,6 @@ int batch_record(rdcnn_batch *b, long long T, float *traj, bool even, const char
         depth = state_depth_cap(b, depth);
     }
     if (depth < 1) return bfail(RDCNN_EINVAL, "%s: packed state too large to record", who);
-    if (cpl != b->rec_cpl) {
-        for (TileTable &t : b->rec_tables)
-            if (t.dev) (void)hipFree(t.dev);
-        b->rec_tables.clear();
-        b->rec_cpl = cpl;
-    }
     long long q = 0;
     if (even && depth >= 2) {
         // As for a single grid: every pass but the last writes its output into
