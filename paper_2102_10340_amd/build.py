@@ -24,9 +24,9 @@ OBJDIR = os.path.join(HERE, "_build")
 SOURCES = ["rd_api.hip", "rd_forward.hip", "rd_adjoint.hip", "rd_batch.hip", "rd_stats.hip",
            "rd_models.hip", "rd_fwd_r0c1.hip", "rd_fwd_r0c2.hip", "rd_fwd_r0c4.hip",
            "rd_fwd_r1c1.hip", "rd_fwd_r1c2.hip", "rd_fwd_r1c4.hip", "rd_fwd_r23.hip",
-           "rd_pair.hip", "rd_tile.hip", "rd_tile_fhn.hip", "rd_tile_gs.hip", "rd_tile_rec.hip",
-           "rd_tile_adj.hip", "rd_batch_whole.hip", "rd_batch_r0.hip", "rd_batch_rec.hip",
-           "rd_adj_plain.hip", "rd_adj_pair.hip", "rd_adj_batch.hip"]
+           "rd_pair.hip", "rd_tile.hip", "rd_tile_fhn.hip", "rd_tile_gs.hip", "rd_tile_cnn.hip",
+           "rd_tile_rec.hip", "rd_tile_adj.hip", "rd_batch_whole.hip", "rd_batch_r0.hip",
+           "rd_batch_rec.hip", "rd_adj_plain.hip", "rd_adj_pair.hip", "rd_adj_batch.hip"]
 ARCH = "gfx950"
 
 FLAGS = [

@@ -305,6 +305,15 @@ struct Pingpong {
     }
 };
 
+// The largest grid of h's kind that takes resident tiles.
+long long max_tile_cells(const rdcnn_sim *h)
+{
+    if (h->model == rd::MODEL_CNN) return rd::kMaxTileCellsCnn;
+    const bool torus_pairs = h->bc == RDCNN_BC_PERIODIC &&
+                             rd::pair_pass(h->bc, h->R, h->C, rd::kPairCpl, rd::kPairDepth);
+    return torus_pairs ? rd::kMaxTileCellsTorus : rd::kMaxTileCells;
+}
+
 // Columns per lane of plain 8-step passes of grids beyond the resident tiles':
 // four where pairs of wavefronts run them, unless the last strip would be mostly
 // idle; else four from 3072^2 on and two below (us per step, zero-flux, four in
@@ -356,8 +365,9 @@ void auto_config(const rdcnn_sim *h, int *cpl, int *depth, int *seg_rows, bool r
 // (the instantiated depths), one step per pass at a zero-flux edge when the
 // update is not mirror-exact for these parameters.
 // Pass shape of a grid of another cell model: the forced settings, else 8
-// steps per pass with plain_cols columns per lane for Gray-Scott; for the CNN 2
-// from 2048^2, 1 below; widths beyond the model's widest are narrowed to it.
+// steps per pass with plain_cols columns per lane for Gray-Scott; for the CNN,
+// beyond the resident tiles or where its halos are not exact, 2 from 2048^2, 1
+// below; widths beyond the model's widest are narrowed to it.
 void model_shape(const rdcnn_sim *h, int *cpl, int *depth, int *seg)
 {
     const int wmax = rd::model_max_cpl(h->model);
@@ -374,15 +384,25 @@ void model_shape(const rdcnn_sim *h, int *cpl, int *depth, int *seg)
     if (*cpl > wmax) *cpl = wmax;
 }
 
+// Whether a grid of another model may take resident tiles: unless a kernel is
+// forced, or its halos would not be exact (one streamed step a pass then).
+bool model_tiles(const rdcnn_sim *h)
+{
+    return h->kind == 0 &&
+           (h->bc == RDCNN_BC_PERIODIC || rd::model_mirror_exact(h->model, h->mparams));
+}
+
 int run_model_steps(rdcnn_sim *h, long long n)
 {
     if (h->kind == 1) return fail(RDCNN_EINVAL, "rdcnn_step: the one-thread-per-cell kernel "
                                                 "exists for FitzHugh-Nagumo only");
     rd::TilePlan plan;
-    if (h->kind == 0 && h->model == rd::MODEL_GRAY_SCOTT && rd::tile_plan(h->R, h->C, h->bc, n, &plan)) {
+    if (model_tiles(h) && rd::tile_plan(h->R, h->C, max_tile_cells(h), n, &plan)) {
+        const auto launch =
+            h->model == rd::MODEL_GRAY_SCOTT ? rd::launch_tile_gs : rd::launch_tile_cnn;
         for (long long i = 0; i < plan.passes; ++i) {
-            const hipError_t e = rd::launch_tile_gs(h->buf[h->cur], h->buf[1 - h->cur], h->R, h->C,
-                                                    h->bc, h->mparams, plan.at(i), h->stream);
+            const hipError_t e = launch(h->buf[h->cur], h->buf[1 - h->cur], h->R, h->C, h->bc,
+                                        h->mparams, plan.at(i), h->stream);
             if (e != hipSuccess) return hip_fail(e, "rdcnn_step: model kernel launch");
             h->cur = 1 - h->cur;
         }
@@ -484,7 +504,7 @@ int run_steps(rdcnn_sim *h, long long n, float *rec, bool rec_even = false, int 
     int kind = h->kind, cpl = h->cpl, depth = h->depth, seg = h->seg_rows;
     if (kind == 0 && !rec) {
         rd::TilePlan plan;
-        if (rd::tile_plan(h->R, h->C, h->bc, n, &plan)) {
+        if (rd::tile_plan(h->R, h->C, max_tile_cells(h), n, &plan)) {
             for (long long i = 0; i < plan.passes; ++i) {
                 const hipError_t e = rd::launch_tile(h->buf[h->cur], h->buf[1 - h->cur], h->R, h->C,
                                                      h->bc, h->g, plan.at(i), h->stream);
@@ -1104,7 +1124,7 @@ int rdcnn_step_checkpoints(rdcnn_t h, long long T, long long S, float *ckpt_dev)
         long long k = kind == 1 ? 1 : depth;
         if (q % S == 0 && tiles) {
             pass = 0;
-            if (bound - q != plan_len) tiles = rd::tile_plan(h->R, h->C, h->bc, bound - q, &plan);
+            if (bound - q != plan_len) tiles = rd::tile_plan(h->R, h->C, max_tile_cells(h), bound - q, &plan);
             plan_len = bound - q;
         }
         if (tiles) k = plan.at(pass).K;
@@ -1385,7 +1405,7 @@ int rdcnn_pass_config(rdcnn_t h, int *kind, int *depth, int *cols_per_lane, int 
         return fail(RDCNN_EINVAL, "rdcnn_pass_config: NULL argument");
     int k = h->kind == 3 ? 2 : h->kind, cpl = h->cpl, d = h->depth, seg = h->seg_rows;
     rd::TilePlan plan;
-    if (h->kind == 0 && h->model != rd::MODEL_CNN && rd::tile_plan(h->R, h->C, h->bc, 1 << 20, &plan)) {
+    if ((h->model == rd::MODEL_FHN ? h->kind == 0 : model_tiles(h)) && rd::tile_plan(h->R, h->C, max_tile_cells(h), 1 << 20, &plan)) {
         *kind = 4;
         *depth = plan.base.K;
         *cols_per_lane = plan.base.cpl;

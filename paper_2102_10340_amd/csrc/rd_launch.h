@@ -105,6 +105,9 @@ constexpr int kMaxTileDepth = 16;
 // 3.91, 2400^2 4.59 / 4.30.
 constexpr long long kMaxTileCells = 6000000;
 constexpr long long kMaxTileCellsTorus = 4500000;  // where pairs are the other choice
+// The CNN (its streamed pass has two columns per lane at most): 2400^2 5.7 / 7.2,
+// 4096^2 14.9 / 17.1, 6000^2 34.5 / 35.5 (a torus 34.8 / 34.3).
+constexpr long long kMaxTileCellsCnn = 32000000;
 inline int tile_out_rows(const TileShape &s) { return 2 * s.w * s.rw - 2 * s.K; }
 
 // T steps as `passes` passes: the first `deeper` of shape `deep`, the others of
@@ -114,9 +117,9 @@ struct TilePlan {
     TileShape base{}, deep{};
     const TileShape &at(long long i) const { return i < deeper ? deep : base; }
 };
-// The fastest plan by the launcher's cost model; false if the grid is for the
-// streamed kernel.
-bool tile_plan(int R, int C, int bc, long long T, TilePlan *plan);
+// The fastest plan by the launcher's cost model; false if the grid has more than
+// max_cells cells and is for the streamed kernels.
+bool tile_plan(int R, int C, long long max_cells, long long T, TilePlan *plan);
 // Recording passes: the (even) depth of the passes of an n-step run, 0 if the
 // grid is for the streamed kernel; the shape of a pass of K steps.
 int tile_record_depth(int R, int C, long long n);
@@ -132,6 +135,8 @@ hipError_t launch_tile(const float *in, float *out, int R, int C, int bc, const 
                        const TileShape &shape, hipStream_t s, const TileRecord *rec = nullptr);
 hipError_t launch_tile_gs(const float *in, float *out, int R, int C, int bc, const float *params,
                           const TileShape &shape, hipStream_t s);
+hipError_t launch_tile_cnn(const float *in, float *out, int R, int C, int bc, const float *params,
+                           const TileShape &shape, hipStream_t s);
 
 // Cell models other than FitzHugh-Nagumo on the same streamed kernel
 // (rd_models.h).  Their passes take depth 1, 2, 4 or 8 and cols_per_lane 1, 2

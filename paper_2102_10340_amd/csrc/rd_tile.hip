@@ -139,14 +139,12 @@ int even_depth(const Table &tb, long long S)
 
 }  // namespace
 
-bool tile_plan(int R, int C, int bc, long long T, TilePlan *plan)
+bool tile_plan(int R, int C, long long max_cells, long long T, TilePlan *plan)
 {
     // Up to here the resident tiles are the faster kind; above, the streamed
     // kernel's wider strips waste less on halos and hide their memory traffic
     // behind the arithmetic.
-    const bool torus_pairs = bc == BC_PERIODIC && pair_pass(bc, R, C, kPairCpl, kPairDepth);
-    const long long most = torus_pairs ? kMaxTileCellsTorus : kMaxTileCells;
-    if ((long long)R * C > most || T < 1) return false;
+    if ((long long)R * C > max_cells || T < 1) return false;
     const Table &tb = table(R, C, false);
     double best = INFINITY;
     for (int K = 1; K <= kMaxTileDepth; ++K) {
@@ -252,6 +250,22 @@ hipError_t launch_tile_gs(const float *in, float *out, int R, int C, int bc, con
     a.rec_stride = 0;
     a.rec_first = 0;
     return launch_tiles(tile_fn_gs(sh.cpl, sh.rw), a, sh, s);
+}
+
+hipError_t launch_tile_cnn(const float *in, float *out, int R, int C, int bc, const float *params,
+                           const TileShape &sh, hipStream_t s)
+{
+    TileStepArgsT<ModelCnn> a;
+    if (!tile_geometry(R, C, bc, sh, &a.t)) return hipErrorInvalidValue;
+    a.in = in;
+    a.out = out;
+    a.g.dt = params[0];
+    for (int k = 0; k < 9; ++k) a.g.A[k] = params[1 + k];
+    a.K = sh.K;
+    a.rec = nullptr;
+    a.rec_stride = 0;
+    a.rec_first = 0;
+    return launch_tiles(tile_fn_cnn(sh.cpl, sh.rw), a, sh, s);
 }
 
 hipError_t launch_tile_adjoint(const AdjPlanes &io, const float *even_states, int every,
