@@ -197,10 +197,10 @@ int rdcnn_set_kernel(rdcnn_t h, int kind, int depth, int cols_per_lane, int seg_
 /*
  * rdcnn_pass_config -- the pass shape later rdcnn_step calls use, with the
  * automatic choices resolved: *kind 1 (one thread per cell), 2 (streamed) or 4
- * (resident tiles, the automatic choice up to about 2400^2 cells; not a kind
- * rdcnn_set_kernel takes), *depth steps per pass (kind 4: of a long run; other
- * runs are cut evenly), *cols_per_lane, *seg_rows output rows per wavefront
- * (kind 4: per workgroup)
+ * (resident tiles, the automatic choice up to 6 million cells, 4.5 on most
+ * tori, 32 for the CNN; not a kind rdcnn_set_kernel takes), *depth steps per
+ * pass (kind 4: of a long run; other runs are cut evenly), *cols_per_lane,
+ * *seg_rows output rows per wavefront (kind 4: per workgroup)
  * (the paper's block/grid choice, Sec. II.B, made explicit).  Host-only, no
  * device work.  Errors: RDCNN_EINVAL (NULL argument).
  */
@@ -479,7 +479,7 @@ int rdcnn_batch_use_graph(rdcnn_batch_t b, int on);
 
 /*
  * rdcnn_batch_use_lds -- on != 0 (the default): instances small enough to sit
- * whole in one workgroup's LDS (at most 16384 cells, (rows+2)*(cols+2) pairs of
+ * whole in one workgroup's LDS (or its registers; at most 16384 cells, (rows+2)*(cols+2) pairs of
  * floats within the device's per-workgroup LDS) run all T steps of a
  * rdcnn_batch_step call in one launch, reading and writing HBM once.  Results
  * are bit-identical either way.  Errors: RDCNN_EINVAL, RDCNN_ENOMEM.

@@ -84,11 +84,12 @@ class Batch:
         check(lib.rdcnn_batch_set_class_seg_rows(self._h, int(rows), int(cols), int(seg_rows)))
 
     def use_lds(self, on: bool = True) -> None:
-        """Run instances that fit one workgroup's LDS whole, all steps in one launch."""
+        """Run instances that fit one workgroup's registers or LDS whole, all steps in
+        one launch."""
         check(lib.rdcnn_batch_use_lds(self._h, 1 if on else 0))
 
     def lds_instances(self) -> int:
-        """How many instances the in-LDS kernel runs."""
+        """How many instances are held whole in one workgroup."""
         n = ctypes.c_int()
         check(lib.rdcnn_batch_lds_instances(self._h, ctypes.byref(n)))
         return n.value

@@ -327,9 +327,9 @@ int plain_cols(const rdcnn_sim *h)
     return h->R >= 3072 && h->C >= 3072 ? 4 : 2;
 }
 
-// Default pass settings for a grid when the caller has not forced any (from
-// sweeps on MI355X: wide strips and deep passes pay off only on large grids;
-// smaller grids are latency bound and want more, narrower wavefronts).
+// Default settings of streamed passes when the caller has not forced any: plain
+// ones of grids beyond the resident tiles', recordings beyond theirs (and full
+// recordings of any grid).
 void auto_config(const rdcnn_sim *h, int *cpl, int *depth, int *seg_rows, bool record,
                  bool record_even = false)
 {

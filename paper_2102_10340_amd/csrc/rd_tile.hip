@@ -11,15 +11,16 @@ namespace {
 constexpr int kCus = 256;
 constexpr int kLdsPerCu = 160 * 1024;
 // VGPRs of the instances, rows per block 1 .. 6 (bounds the wavefronts of a SIMD)
-constexpr int kVgpr2[7] = {0, 34, 42, 49, 57, 67, 79};
-constexpr int kVgpr4[7] = {0, 0, 58, 72, 88, 108, 128};
+constexpr int kVgpr2[7] = {0, 34, 43, 50, 58, 69, 81};
+constexpr int kVgpr4[7] = {0, 0, 59, 72, 89, 111, 128};
 constexpr int kWaves[] = {4, 6, 8, 10, 12, 16};
 
 // Predicted microseconds of one K-step pass.  Fitted to 1500 timed passes on
 // grids of 128^2 to 2048^2, 200x700 and 777x1301 (7 % rms); on each of them the
-// shape it picks is within 1.2 % of the fastest timed one.  The terms: launch and fill; the tile reads and the writes; then per
-// step the VALU work of the workgroups that share a compute unit (never less
-// than one wavefront's own issue), their LDS traffic, and the barrier.
+// shape it picks is within 1.2 % of the fastest timed one.  The terms: launch and
+// fill; the tile reads and the writes; then per step the VALU work of the
+// workgroups that share a compute unit (never less than one wavefront's own
+// issue), their LDS traffic, and the barrier.
 double pass_us(int R, int C, int cpl, int rw, int w, int K, int ntiles)
 {
     const int vg = ((cpl == 4 ? kVgpr4[rw] : kVgpr2[rw]) + 7) / 8 * 8;
@@ -46,7 +47,7 @@ double pass_us(int R, int C, int cpl, int rw, int w, int K, int ntiles)
 // 1500^2 (7 % rms; the picked shape within 2 % of the fastest timed one).
 double adj_pass_us(int R, int C, int cpl, int rw, int w, int K, int ntiles)
 {
-    constexpr int kVgpr[2][5] = {{0, 0, 108, 127, 146}, {0, 0, 168, 203, 242}};
+    constexpr int kVgpr[2][5] = {{0, 0, 112, 136, 162}, {0, 0, 179, 221, 256}};
     const int vg = (kVgpr[cpl == 4][rw] + 7) / 8 * 8;
     int occ = 512 / vg * 4 / w;
     if (occ < 1) occ = 1;

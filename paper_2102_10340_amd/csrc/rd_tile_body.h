@@ -21,7 +21,7 @@
 // are the slow side of LDS here (78 bytes per clock against 200-250 read), which
 // is why only the two outer rows of a block are written.  Measured per step,
 // against the streamed kernel at its tuned shape: 128^2 0.54 us (1.17), 256^2
-// 0.55 (1.23), 512^2 0.75 (1.57), 1024^2 1.39 (2.26), 2048^2 3.6 (4.3).
+// 0.55 (1.23), 512^2 0.75 (1.57), 1024^2 1.39 (2.26), 2048^2 3.33 (4.2).
 #pragma once
 
 #include <type_traits>
