@@ -314,15 +314,15 @@ long long max_tile_cells(const rdcnn_sim *h)
     return torus_pairs ? rd::kMaxTileCellsTorus : rd::kMaxTileCells;
 }
 
-// Columns per lane of plain 8-step passes of grids beyond the resident tiles':
+// Columns per lane of plain k-step passes of grids beyond the resident tiles':
 // four where pairs of wavefronts run them, unless the last strip would be mostly
 // idle; else four from 3072^2 on and two below (us per step, zero-flux, four in
 // pairs / two / one: 2560^2 4.84 / 5.48 / 6.62, 1500x5000 5.33 / 6.16 / 7.33,
 // 12000x600 5.76 / 6.50 / 7.18, 20000x400 6.03 / 7.05 / 8.20; four without pairs /
-// two: 2501x2503 6.25 / 5.45).
-int plain_cols(const rdcnn_sim *h)
+// two: 2501x2503 6.25 / 5.45; a pass of 7 on 2600x2664 49.7 us / 44.1).
+int plain_cols(const rdcnn_sim *h, int k)
 {
-    if (rd::pair_pass(h->bc, h->R, h->C, rd::kPairCpl, rd::kPairDepth) && h->C >= 384)
+    if (rd::pair_pass(h->bc, h->R, h->C, rd::kPairCpl, k) && h->C >= 384)
         return rd::kPairCpl;
     return h->R >= 3072 && h->C >= 3072 ? 4 : 2;
 }
@@ -356,7 +356,7 @@ void auto_config(const rdcnn_sim *h, int *cpl, int *depth, int *seg_rows, bool r
         long long seg = (h->R + want - 1) / want;
         *seg_rows = (int)(seg < 4 ? 4 : seg);
     } else {
-        *cpl = plain_cols(h);
+        *cpl = plain_cols(h, 8);
         *depth = 8;
     }
 }
@@ -375,7 +375,7 @@ void model_shape(const rdcnn_sim *h, int *cpl, int *depth, int *seg)
     *depth = h->depth;
     *seg = h->seg_rows;
     if (h->kind == 0) {
-        *cpl = h->model == rd::MODEL_GRAY_SCOTT ? plain_cols(h)
+        *cpl = h->model == rd::MODEL_GRAY_SCOTT ? plain_cols(h, 8)
                : h->R >= 2048 && h->C >= 2048   ? 2
                                                 : 1;
         *depth = 8;
@@ -414,6 +414,7 @@ int run_model_steps(rdcnn_sim *h, long long n)
     while (n > 0) {
         int k = 8;
         while (k > 1 && (k > depth || k > n)) k >>= 1;
+        if (h->kind == 0 && h->model == rd::MODEL_GRAY_SCOTT) cpl = plain_cols(h, k);
         rd::StreamGeom geom;
         if (!(h->model == rd::MODEL_GRAY_SCOTT
                   ? rd::plain_geometry(h->R, h->C, h->bc, cpl, k, seg, &geom)
@@ -569,6 +570,7 @@ int run_steps(rdcnn_sim *h, long long n, float *rec, bool rec_even = false, int 
             done = 1;
         } else {
             const int k = (int)(n < depth ? n : depth);
+            if (h->kind == 0 && !rec) cpl = plain_cols(h, k);
             rd::StreamGeom geom;
             if (!(rec ? rd::stream_geometry(h->R, h->C, cpl, k, seg, &geom)
                       : rd::plain_geometry(h->R, h->C, h->bc, cpl, k, seg, &geom)))
@@ -1138,6 +1140,7 @@ int rdcnn_step_checkpoints(rdcnn_t h, long long T, long long S, float *ckpt_dev)
         } else if (kind == 1) {
             e = rd::launch_naive(in, out, h->R, h->C, h->bc, h->g, h->stream);
         } else {
+            if (h->kind == 0) cpl = plain_cols(h, (int)k);
             rd::StreamGeom geom;
             if (!rd::plain_geometry(h->R, h->C, h->bc, cpl, (int)k, seg, &geom))
                 return fail(RDCNN_EINVAL, "%s: cannot tile %dx%d with cpl=%d depth=%lld", who, h->R,
@@ -1315,6 +1318,13 @@ int rdcnn_init_backward(const float *adj_dev, long long n, float ka, float *gx_d
     return RDCNN_OK;
 }
 
+// Whether one kernel reads both planes (of `bytes` each): where a state fits the
+// 32 MB of L2, and where it, its partner and the destination pass the 256 MB of the
+// last cache.  In between the next pass ran faster after the copies (steps and a
+// read, kernel / copies, us: 2600x2665, 7 steps, 75 / 64; 1500x5000, 7, 75 / 64;
+// 4096^2, 8, 127 / 139; 128^2, 10, 10 / 12).
+static bool kernel_reads(size_t bytes) { return bytes <= (16u << 20) || bytes > (43u << 20); }
+
 int rdcnn_read(rdcnn_t h, float *u_dst, float *v_dst, int dst_is_host)
 {
     if (!h || !u_dst || !v_dst) return fail(RDCNN_EINVAL, "rdcnn_read: NULL argument");
@@ -1326,9 +1336,9 @@ int rdcnn_read(rdcnn_t h, float *u_dst, float *v_dst, int dst_is_host)
         e = hipMemcpyAsync(u_dst, s, bytes, hipMemcpyDeviceToHost, h->stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(v_dst, s + n, bytes, hipMemcpyDeviceToHost, h->stream);
-    } else if (on_device_of(s, u_dst) && on_device_of(s, v_dst)) {
+    } else if (kernel_reads(bytes) && on_device_of(s, u_dst) && on_device_of(s, v_dst)) {
         e = rd::launch_copy_planes(s, (long long)n, u_dst, v_dst, h->stream);
-    } else {  // another device's memory, or the host's: the copies find their way
+    } else {  // also another device's memory, or the host's: the copies find their way
         e = hipMemcpyAsync(u_dst, s, bytes, hipMemcpyDeviceToDevice, h->stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(v_dst, s + n, bytes, hipMemcpyDeviceToDevice, h->stream);

@@ -166,9 +166,8 @@ struct Tile {
         y0 = ry0;
         y1 = ry1;
         cx = x0 + CPL * (int)threadIdx.x;
-        // a strip inside the grid, or a torus of whole vectors, where a lane's columns
-        // stay together as they wrap (a buffer access needs 4-byte alignment only)
-        fast = (x0 >= 0 && x0 + 64 * CPL <= A.C) || (A.vec_ok && A.bc == BC_PERIODIC);
+        // on a torus of whole vectors a lane's columns stay together where they wrap
+        fast = A.vec_ok && (A.bc == BC_PERIODIC || (x0 >= 0 && x0 + 64 * CPL <= A.C));
         edge = A.anchored && (x0 == 0 || x0 + 64 * CPL == A.C);
 #pragma unroll
         for (int e = 0; e < CPL; ++e) mo[e] = 4u * (unsigned)map_index(cx + e, A.C, A.bc);
