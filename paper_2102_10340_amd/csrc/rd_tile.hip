@@ -64,12 +64,6 @@ double adj_pass_us(int R, int C, int cpl, int rw, int w, int K, int ntiles)
     return 2.93 + mb / 3.42 + rounds * K * step / 2400.0;
 }
 
-struct Table {
-    int R = -1, C = -1;
-    TileShape best[kMaxTileDepth + 1];
-    double us[kMaxTileDepth + 1];
-};
-
 // Output columns of a tile, and tiles of an R x C grid (0: the shape has no output).
 int tile_out_cols(const TileShape &s)
 {
@@ -82,16 +76,35 @@ long long tiles_of(int R, int C, const TileShape &s)
     return ((long long)C + wout - 1) / wout * (((long long)R + h - 1) / h);
 }
 
-// Fastest shape for each pass depth on an R x C grid (adj: of the reverse
-// passes, whose depths are even).
-void fill_table(Table &tb, int R, int C, bool adj)
-{
-    tb.R = R;
-    tb.C = C;
-    for (int K = 1; K <= kMaxTileDepth; ++K) {
-        tb.us[K] = INFINITY;
-        tb.best[K] = TileShape{0, 0, 0, 0};
-        if (adj && ((K & 1) || K > 12)) continue;
+// Fastest shapes of the passes on one grid size (adj: of the reverse passes, whose
+// depths are even), each depth's found when it is first asked for: 1.1 us of host
+// time a depth (all 16: 17 us), which a 10-step run of 128^2 in 9.6 us would pay
+// for depths it cannot use.
+struct Table {
+    int R = 0, C = 0;
+    bool adj = false;
+    unsigned known = 0;  // bit K: depth K is filled in
+    TileShape best[kMaxTileDepth + 1];
+    double cost[kMaxTileDepth + 1];
+
+    double us(int K)
+    {
+        if (!(known >> K & 1)) fill(K);
+        return cost[K];
+    }
+    const TileShape &shape(int K)
+    {
+        us(K);
+        return best[K];
+    }
+
+private:
+    void fill(int K)
+    {
+        known |= 1u << K;
+        cost[K] = INFINITY;
+        best[K] = TileShape{0, 0, 0, 0};
+        if (adj && ((K & 1) || K > 12)) return;
         for (int cpl = 2; cpl <= 4; cpl += 2)
             for (int rw = adj ? 2 : cpl / 2; rw <= (adj ? 4 : 6); ++rw)
                 for (int w : kWaves) {
@@ -99,38 +112,54 @@ void fill_table(Table &tb, int R, int C, bool adj)
                     const TileShape sh{cpl, rw, w, K};
                     const long long nt = tiles_of(R, C, sh);
                     if (nt < 1 || nt > 1 << 22) continue;
-                    const double us = (adj ? adj_pass_us : pass_us)(R, C, cpl, rw, w, K, (int)nt);
-                    if (us < tb.us[K]) {
-                        tb.us[K] = us;
-                        tb.best[K] = sh;
+                    const double t = (adj ? adj_pass_us : pass_us)(R, C, cpl, rw, w, K, (int)nt);
+                    if (t < cost[K]) {
+                        cost[K] = t;
+                        best[K] = sh;
                     }
                 }
     }
+};
+
+// The tables of a thread's last kTables sizes (20 KB): a program that makes a handle
+// per call finds its size again, and one that steps several live grids in turn finds
+// each of theirs.  10 steps and a read of 128^2 and of 256^2 in turn: 32.6 us with
+// one size kept, 19.0 with these (31.3 on the streamed kernel).
+constexpr int kTables = 48;
+Table &table(int R, int C, bool adj)
+{
+    static thread_local Table tb[kTables];
+    static thread_local int last = 0, next = 0;
+    if (tb[last].R == R && tb[last].C == C && tb[last].adj == adj) return tb[last];
+    for (last = 0; last < kTables; ++last)
+        if (tb[last].R == R && tb[last].C == C && tb[last].adj == adj) return tb[last];
+    last = next;
+    next = (next + 1) % kTables;
+    tb[last].R = R;
+    tb[last].C = C;
+    tb[last].adj = adj;
+    tb[last].known = 0;
+    return tb[last];
 }
 
-// The tables of the last grid size, per thread (a program that makes a handle
-// per call fills them once).
-const Table &table(int R, int C, bool adj)
-{
-    static thread_local Table tb[2];
-    Table &t = tb[adj];
-    if (t.R != R || t.C != C) fill_table(t, R, C, adj);
-    return t;
-}
+// No pass is predicted to take less (pass_us, adj_pass_us): plans of more passes
+// than the best one's time holds need not be looked at.
+constexpr double kLeastPassUs = 2.9;
 
 // The even depth of the passes through S steps with the least total time: of
 // each number of passes, equally deep ones.
-int even_depth(const Table &tb, long long S)
+int even_depth(Table &tb, long long S)
 {
     int best = 2;
     double least = INFINITY;
-    for (int K = 2; K <= kMaxTileDepth; K += 2) {
+    for (int K = kMaxTileDepth; K >= 2; K -= 2) {
         const long long n = (S + K - 1) / K;
+        if ((double)n * kLeastPassUs > least) break;
         int d = (int)((S + n - 1) / n);
         d += d & 1;
         const int last = (int)(S - (n - 1) * d);  // > 0: d <= K
-        const double us = (double)(n - 1) * tb.us[d] + tb.us[last + (last & 1)];
-        if (us < least) {
+        const double us = (double)(n - 1) * tb.us(d) + tb.us(last + (last & 1));
+        if (us <= least) {
             least = us;
             best = d;
         }
@@ -146,19 +175,21 @@ bool tile_plan(int R, int C, long long max_cells, long long T, TilePlan *plan)
     // kernel's wider strips waste less on halos and hide their memory traffic
     // behind the arithmetic.
     if ((long long)R * C > max_cells || T < 1) return false;
-    const Table &tb = table(R, C, false);
+    Table &tb = table(R, C, false);
     double best = INFINITY;
-    for (int K = 1; K <= kMaxTileDepth; ++K) {
+    for (int K = kMaxTileDepth; K >= 1; --K) {
         const long long n = (T + K - 1) / K;  // passes, of two depths that differ by one
+        if ((double)n * kLeastPassUs > best) break;
         const long long lo = T / n, more = T % n;
         if (more && lo + 1 > kMaxTileDepth) continue;
-        const double us = (double)(n - more) * tb.us[lo] + (more ? (double)more * tb.us[lo + 1] : 0.0);
-        if (us < best) {
+        const double us =
+            (double)(n - more) * tb.us((int)lo) + (more ? (double)more * tb.us((int)lo + 1) : 0.0);
+        if (us <= best) {
             best = us;
             plan->passes = n;
             plan->deeper = more;
-            plan->base = tb.best[lo];
-            plan->deep = tb.best[more ? lo + 1 : lo];
+            plan->base = tb.shape((int)lo);
+            plan->deep = tb.shape((int)(more ? lo + 1 : lo));
         }
     }
     return best < INFINITY;
@@ -170,7 +201,7 @@ int tile_record_depth(int R, int C, long long n)
     return even_depth(table(R, C, false), n);
 }
 
-TileShape tile_shape(int R, int C, int K) { return table(R, C, false).best[K]; }
+TileShape tile_shape(int R, int C, int K) { return table(R, C, false).shape(K); }
 
 int tile_adjoint_depth(int R, int C, long long S)
 {
@@ -178,7 +209,7 @@ int tile_adjoint_depth(int R, int C, long long S)
     return even_depth(table(R, C, true), S);
 }
 
-TileShape tile_adjoint_shape(int R, int C, int K) { return table(R, C, true).best[K]; }
+TileShape tile_adjoint_shape(int R, int C, int K) { return table(R, C, true).shape(K); }
 
 long long tile_adjoint_slots(int R, int C, int K)
 {
