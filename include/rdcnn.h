@@ -361,8 +361,9 @@ int rdcnn_step_bwd_ckpt(rdcnn_t h, const float *ckpt_dev, long long T, long long
  * results (bit for bit) as rdcnn_step_bwd; the per-tile partial sums live in
  * a static device array of the library instead of the pooled buffer, so the
  * call makes no hipMalloc, hipFree or other allocation.  Limit: the reverse
- * passes may use at most 65536 tiles (4 MiB of partial sums; the automatic
- * pass shape uses about 2600 on any grid up to 2^30 cells); more is rejected
+ * passes may use at most 65536 slots of partial sums (4 MiB: one per tile, or
+ * per wavefront of a resident tile; the automatic pass shapes need no more on
+ * grids of up to 3 million columns); more is rejected
  * with RDCNN_EINVAL and a message naming the count.  The array is resolved
  * once per device (at rdcnn_create, or at the first call on a device) and
  * stays allocated until the process ends.  Every call on one device shares

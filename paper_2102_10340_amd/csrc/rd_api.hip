@@ -947,17 +947,27 @@ int plan_pairs(const rdcnn_sim *h, long long S, int every, const char *who, Pair
     // An odd S starts with one plain reverse step (state s_{S-1} is even);
     // then paired passes of `depth` steps and one shorter even remainder.
     const long long even = S & ~1LL;
-    const int tile_depth = h->adj_depth == 0 ? rd::tile_adjoint_depth(h->R, h->C, even) : 0;
-    if (tile_depth > 0) depth = tile_depth;
-    const int klast = even == 0 ? 0 : (int)(even % depth == 0 ? depth : even % depth);
+    int tile_depth = h->adj_depth == 0 ? rd::tile_adjoint_depth(h->R, h->C, even) : 0;
+    auto first_of = [&](int d) { return (int)(even < d ? even : d); };
+    auto last_of = [&](int d) { return even == 0 ? 0 : (int)(even % d == 0 ? d : even % d); };
     long long need = 0;
-    for (int k : {(S & 1) ? 1 : 0, (int)(even < depth ? even : depth), klast}) {
-        if (k == 0) continue;
-        if (tile_depth > 0 && k > 1) {
+    if (tile_depth > 0) {
+        for (int k : {first_of(tile_depth), last_of(tile_depth)}) {
             const long long slots = rd::tile_adjoint_slots(h->R, h->C, k);
             if (slots > need) need = slots;
-            continue;
         }
+        // Resident tiles take a slot per wavefront, which on thin grids is more
+        // than the static workspace holds (2 x 1000000: 76924; the streamed pairs
+        // need 2560 to 41000 there).  The pairs run them for every entry point,
+        // as the results of all are the same.
+        if (need > kNoAllocTiles) tile_depth = 0;
+    }
+    if (tile_depth > 0)
+        depth = tile_depth;
+    else
+        need = 0;
+    for (int k : {(S & 1) ? 1 : 0, first_of(depth), last_of(depth)}) {
+        if (k == 0 || (tile_depth > 0 && k > 1)) continue;
         rd::StreamGeom gk;
         if (!rd::stream_geometry(h->R, h->C, cpl, k, seg, &gk))
             return fail(RDCNN_EINVAL, "%s: cannot tile %dx%d", who, h->R, h->C);
