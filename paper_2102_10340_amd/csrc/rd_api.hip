@@ -316,15 +316,23 @@ long long max_tile_cells(const rdcnn_sim *h)
 
 // Columns per lane of plain k-step passes of grids beyond the resident tiles':
 // four where pairs of wavefronts run them, unless the last strip would be mostly
-// idle; else four from 3072^2 on and two below (us per step, zero-flux, four in
-// pairs / two / one: 2560^2 4.84 / 5.48 / 6.62, 1500x5000 5.33 / 6.16 / 7.33,
+// idle; else four from 3072^2 on and two from 2048^2 on (us per step, zero-flux,
+// four in pairs / two / one: 2560^2 4.84 / 5.48 / 6.62, 1500x5000 5.33 / 6.16 / 7.33,
 // 12000x600 5.76 / 6.50 / 7.18, 20000x400 6.03 / 7.05 / 8.20; four without pairs /
-// two: 2501x2503 6.25 / 5.45; a pass of 7 on 2600x2664 49.7 us / 44.1).
+// two: 2501x2503 6.25 / 5.45; a pass of 7 on 2600x2664 49.7 us / 44.1).  Of other
+// grids, narrow ones fill few columns of a strip: one, unless two make the strips
+// an eighth narrower together (8 steps, us, one / two: 200000x40 72 / 119, 2000000x4
+// 619 / 1063, 100000x70 72 / 66, 100000x100 103 / 66).
 int plain_cols(const rdcnn_sim *h, int k)
 {
     if (rd::pair_pass(h->bc, h->R, h->C, rd::kPairCpl, k) && h->C >= 384)
         return rd::kPairCpl;
-    return h->R >= 3072 && h->C >= 3072 ? 4 : 2;
+    if (h->R >= 2048 && h->C >= 2048) return h->R >= 3072 && h->C >= 3072 ? 4 : 2;
+    rd::StreamGeom one, two;
+    if (!rd::stream_geometry(h->R, h->C, 1, k, 0, &one) ||
+        !rd::stream_geometry(h->R, h->C, 2, k, 0, &two))
+        return 2;
+    return 9 * one.nstrips < 8 * 2 * two.nstrips ? 1 : 2;
 }
 
 // Default settings of streamed passes when the caller has not forced any: plain
