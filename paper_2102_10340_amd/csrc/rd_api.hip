@@ -305,16 +305,19 @@ struct Pingpong {
     }
 };
 
-// The largest grid of h's kind that takes resident tiles.
-long long max_tile_cells(const rdcnn_sim *h)
+// Whether a T-step run of plain passes takes resident tiles: unless a kernel is
+// forced, or (other models) its halos would not be exact (one streamed step a pass
+// then).
+bool plan_tiles(const rdcnn_sim *h, long long T, rd::TilePlan *plan)
 {
-    if (h->model == rd::MODEL_CNN) return rd::kMaxTileCellsCnn;
-    const bool torus_pairs = h->bc == RDCNN_BC_PERIODIC &&
-                             rd::pair_pass(h->bc, h->R, h->C, rd::kPairCpl, rd::kPairDepth);
-    return torus_pairs ? rd::kMaxTileCellsTorus : rd::kMaxTileCells;
+    if (h->kind != 0) return false;
+    if (h->model != rd::MODEL_FHN && h->bc != RDCNN_BC_PERIODIC &&
+        !rd::model_mirror_exact(h->model, h->mparams))
+        return false;
+    return rd::tile_plan(h->R, h->C, h->bc, h->model, T, plan);
 }
 
-// Columns per lane of plain k-step passes of grids beyond the resident tiles':
+// Columns per lane of streamed plain k-step passes.  Grids beyond kMidTileCells:
 // four where pairs of wavefronts run them, unless the last strip would be mostly
 // idle; else four from 3072^2 on and two from 2048^2 on (us per step, zero-flux,
 // four in pairs / two / one: 2560^2 4.84 / 5.48 / 6.62, 1500x5000 5.33 / 6.16 / 7.33,
@@ -325,9 +328,11 @@ long long max_tile_cells(const rdcnn_sim *h)
 // 619 / 1063, 100000x70 72 / 66, 100000x100 103 / 66).
 int plain_cols(const rdcnn_sim *h, int k)
 {
-    if (rd::pair_pass(h->bc, h->R, h->C, rd::kPairCpl, k) && h->C >= 384)
+    const bool mid = (long long)h->R * h->C <= rd::kMidTileCells;
+    if (!mid && rd::pair_pass(h->bc, h->R, h->C, rd::kPairCpl, k) && h->C >= 384)
         return rd::kPairCpl;
     if (h->R >= 2048 && h->C >= 2048) return h->R >= 3072 && h->C >= 3072 ? 4 : 2;
+    if (mid) return 1;  // latency bound: narrower wavefronts, and more of them
     rd::StreamGeom one, two;
     if (!rd::stream_geometry(h->R, h->C, 1, k, 0, &one) ||
         !rd::stream_geometry(h->R, h->C, 2, k, 0, &two))
@@ -392,20 +397,12 @@ void model_shape(const rdcnn_sim *h, int *cpl, int *depth, int *seg)
     if (*cpl > wmax) *cpl = wmax;
 }
 
-// Whether a grid of another model may take resident tiles: unless a kernel is
-// forced, or its halos would not be exact (one streamed step a pass then).
-bool model_tiles(const rdcnn_sim *h)
-{
-    return h->kind == 0 &&
-           (h->bc == RDCNN_BC_PERIODIC || rd::model_mirror_exact(h->model, h->mparams));
-}
-
 int run_model_steps(rdcnn_sim *h, long long n)
 {
     if (h->kind == 1) return fail(RDCNN_EINVAL, "rdcnn_step: the one-thread-per-cell kernel "
                                                 "exists for FitzHugh-Nagumo only");
     rd::TilePlan plan;
-    if (model_tiles(h) && rd::tile_plan(h->R, h->C, max_tile_cells(h), n, &plan)) {
+    if (plan_tiles(h, n, &plan)) {
         const auto launch =
             h->model == rd::MODEL_GRAY_SCOTT ? rd::launch_tile_gs : rd::launch_tile_cnn;
         for (long long i = 0; i < plan.passes; ++i) {
@@ -511,17 +508,15 @@ int run_steps(rdcnn_sim *h, long long n, float *rec, bool rec_even = false, int 
     }
     long long q = 0;
     int kind = h->kind, cpl = h->cpl, depth = h->depth, seg = h->seg_rows;
-    if (kind == 0 && !rec) {
-        rd::TilePlan plan;
-        if (rd::tile_plan(h->R, h->C, max_tile_cells(h), n, &plan)) {
-            for (long long i = 0; i < plan.passes; ++i) {
-                const hipError_t e = rd::launch_tile(h->buf[h->cur], h->buf[1 - h->cur], h->R, h->C,
-                                                     h->bc, h->g, plan.at(i), h->stream);
-                if (e != hipSuccess) return hip_fail(e, "rdcnn_step: kernel launch");
-                h->cur = 1 - h->cur;
-            }
-            return RDCNN_OK;
+    rd::TilePlan plan;
+    if (!rec && plan_tiles(h, n, &plan)) {
+        for (long long i = 0; i < plan.passes; ++i) {
+            const hipError_t e = rd::launch_tile(h->buf[h->cur], h->buf[1 - h->cur], h->R, h->C,
+                                                 h->bc, h->g, plan.at(i), h->stream);
+            if (e != hipSuccess) return hip_fail(e, "rdcnn_step: kernel launch");
+            h->cur = 1 - h->cur;
         }
+        return RDCNN_OK;
     }
     if (kind == 3) kind = rec ? 0 : 2;  // forced shape for plain steps only
     if (kind == 0 && rec && rec_even && n > 0) {
@@ -1144,7 +1139,7 @@ int rdcnn_step_checkpoints(rdcnn_t h, long long T, long long S, float *ckpt_dev)
         long long k = kind == 1 ? 1 : depth;
         if (q % S == 0 && tiles) {
             pass = 0;
-            if (bound - q != plan_len) tiles = rd::tile_plan(h->R, h->C, max_tile_cells(h), bound - q, &plan);
+            if (bound - q != plan_len) tiles = plan_tiles(h, bound - q, &plan);
             plan_len = bound - q;
         }
         if (tiles) k = plan.at(pass).K;
@@ -1433,7 +1428,7 @@ int rdcnn_pass_config(rdcnn_t h, int *kind, int *depth, int *cols_per_lane, int 
         return fail(RDCNN_EINVAL, "rdcnn_pass_config: NULL argument");
     int k = h->kind == 3 ? 2 : h->kind, cpl = h->cpl, d = h->depth, seg = h->seg_rows;
     rd::TilePlan plan;
-    if ((h->model == rd::MODEL_FHN ? h->kind == 0 : model_tiles(h)) && rd::tile_plan(h->R, h->C, max_tile_cells(h), 1 << 20, &plan)) {
+    if (plan_tiles(h, 1 << 20, &plan)) {
         *kind = 4;
         *depth = plan.base.K;
         *cols_per_lane = plan.base.cpl;

@@ -98,16 +98,6 @@ struct TileShape {
     int cpl, rw, w, K;
 };
 constexpr int kMaxTileDepth = 16;
-// Largest grids that take them.  us per step, resident tiles against pairs of
-// wavefronts on a zero-flux grid: 2048^2 3.33 / 4.07, 2304^2 4.50 / 4.62, 2400^2
-// 4.53 / 4.67 (the pairs reach 4.84 at 2560^2); on a torus, whose strips all take
-// the pairs' short path: 3600x1200 3.54 / 3.49, 2048^2 3.35 / 3.75, 2200^2 4.34 /
-// 3.91, 2400^2 4.59 / 4.30.
-constexpr long long kMaxTileCells = 6000000;
-constexpr long long kMaxTileCellsTorus = 4500000;  // where pairs are the other choice
-// The CNN (its streamed pass has two columns per lane at most): 2400^2 5.7 / 7.2,
-// 4096^2 14.9 / 17.1, 6000^2 34.5 / 35.5 (a torus 34.8 / 34.3).
-constexpr long long kMaxTileCellsCnn = 32000000;
 inline int tile_out_rows(const TileShape &s) { return 2 * s.w * s.rw - 2 * s.K; }
 
 // T steps as `passes` passes: the first `deeper` of shape `deep`, the others of
@@ -117,9 +107,12 @@ struct TilePlan {
     TileShape base{}, deep{};
     const TileShape &at(long long i) const { return i < deeper ? deep : base; }
 };
-// The fastest plan by the launcher's cost model; false if the grid has more than
-// max_cells cells and is for the streamed kernels.
-bool tile_plan(int R, int C, long long max_cells, long long T, TilePlan *plan);
+// The fastest plan of a T-step run of plain passes by the launcher's cost model;
+// false if the run is for the streamed kernels (model: MODEL_*).
+bool tile_plan(int R, int C, int bc, int model, long long T, TilePlan *plan);
+// Cells up to which every run of six steps and more takes resident tiles, unless
+// the grid is narrow.
+constexpr long long kMidTileCells = 4300000;
 // Recording passes: the (even) depth of the passes of an n-step run, 0 if the
 // grid is for the streamed kernel; the shape of a pass of K steps.
 int tile_record_depth(int R, int C, long long n);

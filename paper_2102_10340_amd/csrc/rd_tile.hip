@@ -169,12 +169,47 @@ int even_depth(Table &tb, long long S)
 
 }  // namespace
 
-bool tile_plan(int R, int C, long long max_cells, long long T, TilePlan *plan)
+namespace {
+
+// Whether a grid fills its tiles: one a few cells wide spends them on columns (or
+// rows) folded into the halo, unless it is small enough to be bound by launches.
+// Slow-down on a run of 8 steps against the streamed kernel: 4x500000 1.26, 2x1000000
+// 1.39, 1x3000000 1.35, 3000000x1 1.49, 100000x3 1.35, 100000x40 (a torus) 1.22; speed-up:
+// 10000x64 1.40, 100x20000 1.30, 10000x33 1.46.
+bool fills_tiles(int R, int C)
 {
-    // Up to here the resident tiles are the faster kind; above, the streamed
-    // kernel's wider strips waste less on halos and hide their memory traffic
-    // behind the arithmetic.
-    if ((long long)R * C > max_cells || T < 1) return false;
+    const long long n = (long long)R * C;
+    const int m = R < C ? R : C;
+    return m >= 64 || (m >= 16 && n <= 1 << 19) || n <= 1 << 16;
+}
+
+// Whether a T-step run of plain passes is faster on resident tiles, whose plan
+// would have passes of K steps.  From 9000 timed passes on 60 sizes; speed-up over
+// the streamed passes in brackets.
+// Few steps are bound by memory, which a tile does not touch while it computes:
+// 777x1301 3 steps (0.94), 2000x600 5 (0.95 on a torus), 1792^2 2 (0.79); six steps
+// gain from 1.0 (2048^2) to 1.2.  The other models' streamed passes have 1, 2, 4 or 8
+// steps, so 3 and 5 take them two (3 steps, Gray-Scott: 256^2 1.9, 1536^2 1.5).
+// From 4.3M cells on the streamed passes fill the chip and only deep tiles gain:
+// 2400^2, where pairs of wavefronts are the other choice, 11 steps a pass (0.97), 12
+// (1.04), 16 (1.07); without pairs 2300x2301 8 (0.86), 9 (1.27), 11 (1.05), 16 (1.07).
+// The CNN's streamed pass has two columns per lane at most: 2300x2298 8 (1.00),
+// 2448^2 8 (1.21), 3000^2 8 (1.16); 4096^2 8 (0.98), 12 (1.16), 14 (1.06), 16 (1.03).
+bool tiles_pay(int R, int C, int bc, int model, int K)
+{
+    const long long n = (long long)R * C;
+    if (n <= kMidTileCells) return true;
+    if (model == MODEL_CNN) return n <= 12000000 ? K >= 8 : n <= 20000000 && K >= 10 && K <= 13;
+    if (!pair_pass(bc, R, C, kPairCpl, kPairDepth)) return n <= 6000000 && K >= 9;
+    return K >= 12 && n <= (bc == BC_PERIODIC ? 4500000 : 6000000);
+}
+
+}  // namespace
+
+bool tile_plan(int R, int C, int bc, int model, long long T, TilePlan *plan)
+{
+    if ((long long)R * C > 20000000 || !fills_tiles(R, C)) return false;
+    if (T < 6 && (model == MODEL_FHN || (T != 3 && T != 5))) return false;
     Table &tb = table(R, C, false);
     double best = INFINITY;
     for (int K = kMaxTileDepth; K >= 1; --K) {
@@ -192,12 +227,12 @@ bool tile_plan(int R, int C, long long max_cells, long long T, TilePlan *plan)
             plan->deep = tb.shape((int)(more ? lo + 1 : lo));
         }
     }
-    return best < INFINITY;
+    return best < INFINITY && tiles_pay(R, C, bc, model, plan->base.K);
 }
 
 int tile_record_depth(int R, int C, long long n)
 {
-    if ((long long)R * C > kMaxTileCells || n < 1) return 0;
+    if ((long long)R * C > 6000000 || n < 1) return 0;
     return even_depth(table(R, C, false), n);
 }
 

@@ -4,6 +4,7 @@ import ctypes
 import time
 
 import numpy as np
+import pytest
 
 from paper_2102_10340_amd import _lib
 
@@ -49,3 +50,42 @@ def test_a_new_size_is_cheap():
     for r, c in sizes:
         tile_shape(r, c, 10)
     assert (time.perf_counter() - t) / len(sizes) * 1e6 < 8.0
+
+
+tile_plan = _lib.lib._ZN2rd9tile_planEiiiixPNS_8TilePlanE
+tile_plan.argtypes = [ctypes.c_int] * 4 + [ctypes.c_longlong, ctypes.c_void_p]
+tile_plan.restype = ctypes.c_bool
+FHN, GRAY_SCOTT, CNN = 0, 1, 2
+
+
+def _plan(R, C, T, model=FHN, bc=1):
+    p = Plan()
+    return p if tile_plan(R, C, bc, model, T, ctypes.byref(p)) else None
+
+
+@pytest.mark.parametrize("bc", [0, 1])
+@pytest.mark.parametrize("R,C,T,model", [
+    # few steps are bound by memory
+    (777, 1301, 3, FHN), (2048, 2048, 1, FHN), (1792, 1792, 2, FHN), (2000, 600, 5, FHN),
+    (1280, 1280, 4, GRAY_SCOTT), (2300, 2301, 2, CNN),
+    # grids a few cells wide
+    (4, 500000, 8, FHN), (2, 1000000, 50, FHN), (3000000, 1, 100, FHN), (100000, 40, 7, FHN),
+    (100000, 3, 8, GRAY_SCOTT), (1, 3000000, 16, CNN),
+    # grids on which the streamed passes fill the chip
+    (2300, 2301, 8, FHN), (2400, 2400, 8, FHN), (2400, 2400, 11, FHN), (2300, 2298, 8, GRAY_SCOTT),
+    (3100, 3333, 4, CNN), (4096, 4096, 8, CNN), (2500, 2500, 1000, FHN), (6000, 6000, 12, CNN)])
+def test_runs_the_streamed_passes_are_faster_at(R, C, T, model, bc):
+    assert _plan(R, C, T, model, bc) is None
+
+
+@pytest.mark.parametrize("bc", [0, 1])
+@pytest.mark.parametrize("R,C,T,model", [
+    (1, 1, 10, FHN), (128, 128, 10, FHN), (256, 256, 1000, FHN), (777, 1301, 300, FHN),
+    (1024, 1024, 6, FHN), (10000, 33, 8, FHN), (2048, 2048, 1000, FHN), (2300, 2301, 9, FHN),
+    (2048, 2048, 200, GRAY_SCOTT), (256, 256, 3, GRAY_SCOTT), (512, 512, 5, CNN),
+    (2603, 2900, 39, CNN), (4096, 4096, 12, CNN)])
+def test_runs_the_resident_tiles_are_faster_at(R, C, T, model, bc):
+    p = _plan(R, C, T, model, bc)
+    assert p is not None
+    assert p.deeper * p.deep.K + (p.passes - p.deeper) * p.base.K == T
+    assert p.deeper == 0 or p.deep.K == p.base.K + 1
