@@ -1331,13 +1331,6 @@ int rdcnn_init_backward(const float *adj_dev, long long n, float ka, float *gx_d
     return RDCNN_OK;
 }
 
-// Whether one kernel reads both planes (of `bytes` each): where a state fits the
-// 32 MB of L2, and where it, its partner and the destination pass the 256 MB of the
-// last cache.  In between the next pass ran faster after the copies (steps and a
-// read, kernel / copies, us: 2600x2665, 7 steps, 75 / 64; 1500x5000, 7, 75 / 64;
-// 4096^2, 8, 127 / 139; 128^2, 10, 10 / 12).
-static bool kernel_reads(size_t bytes) { return bytes <= (16u << 20) || bytes > (43u << 20); }
-
 int rdcnn_read(rdcnn_t h, float *u_dst, float *v_dst, int dst_is_host)
 {
     if (!h || !u_dst || !v_dst) return fail(RDCNN_EINVAL, "rdcnn_read: NULL argument");
@@ -1349,7 +1342,7 @@ int rdcnn_read(rdcnn_t h, float *u_dst, float *v_dst, int dst_is_host)
         e = hipMemcpyAsync(u_dst, s, bytes, hipMemcpyDeviceToHost, h->stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(v_dst, s + n, bytes, hipMemcpyDeviceToHost, h->stream);
-    } else if (kernel_reads(bytes) && on_device_of(s, u_dst) && on_device_of(s, v_dst)) {
+    } else if (rd::kernel_reads(n) && on_device_of(s, u_dst) && on_device_of(s, v_dst)) {
         e = rd::launch_copy_planes(s, (long long)n, u_dst, v_dst, h->stream);
     } else {  // also another device's memory, or the host's: the copies find their way
         e = hipMemcpyAsync(u_dst, s, bytes, hipMemcpyDeviceToDevice, h->stream);

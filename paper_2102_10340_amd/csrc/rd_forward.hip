@@ -142,6 +142,13 @@ __global__ __launch_bounds__(256) void copy_planes_kernel(const float *__restric
     }
 }
 
+// Whether one kernel reads both planes of n cells: where the two submissions of the
+// copies are what a read takes.  Beyond, the copies are as fast, and after the
+// kernel the next streamed pass is up to a fifth slower (steps and a read, kernel /
+// copies, us: 128^2, 8 steps, 11.6 / 17.4; 1024x1536, 8, 20.8 / 22.0; 1500^2, 5, 24.5 /
+// 23.4; 2600x2665, 8, 77 / 64; 4096^2, 8, 129 / 139, but the CNN's 233 / 194).
+bool kernel_reads(long long n) { return n <= 1600000; }
+
 hipError_t launch_copy_planes(const float *src, long long n, float *u, float *v, hipStream_t s)
 {
     const int vec = n % 4 == 0 && ((uintptr_t)src | (uintptr_t)u | (uintptr_t)v) % 16 == 0;
