@@ -227,21 +227,39 @@ int side_stream(hipStream_t *out, const char *who)
 
 }  // namespace
 
-namespace {
-
-// Whether p is plain device memory of the device that holds `ref`.
-bool on_device_of(const void *ref, const void *p)
+// Whether a kernel may read the n-cell planes at src and src + n into u and v in place
+// of two copies: all in plain memory of one device, aligned, inside their allocations
+// (a copy past one is refused, a kernel would write there) and apart (a second copy
+// reads what the first has written).
+bool rd::kernel_may_read(const float *src, long long n, const float *u, const float *v)
 {
-    hipPointerAttribute_t a, b;
-    if (hipPointerGetAttributes(&a, ref) == hipSuccess &&
-        hipPointerGetAttributes(&b, p) == hipSuccess)
-        return a.type == hipMemoryTypeDevice && b.type == hipMemoryTypeDevice && a.device == b.device &&
-               !b.isManaged;
-    (void)hipGetLastError();  // an unregistered pointer is no error here
-    return false;
+    const size_t plane = sizeof(float) * (size_t)n;
+    const struct {
+        const float *p;
+        size_t bytes;
+    } at[3] = {{src, 2 * plane}, {u, plane}, {v, plane}};
+    int device = -1;
+    for (int i = 0; i < 3; ++i) {
+        const char *p = (const char *)at[i].p;
+        for (int j = 0; j < i; ++j) {
+            const char *q = (const char *)at[j].p;
+            if (p < q + at[j].bytes && q < p + at[i].bytes) return false;
+        }
+        hipPointerAttribute_t a;
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        if ((uintptr_t)p % sizeof(float) != 0) return false;
+        if (hipPointerGetAttributes(&a, p) != hipSuccess ||
+            hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
+            (void)hipGetLastError();  // an unregistered pointer is no error here
+            return false;
+        }
+        if (a.type != hipMemoryTypeDevice || a.isManaged || (i > 0 && a.device != device)) return false;
+        if (p < (const char *)base || p + at[i].bytes > (const char *)base + size) return false;
+        device = a.device;
+    }
+    return true;
 }
-
-}  // namespace
 
 int rd::check_finite_state(const float *x, long long n, int **flag, hipStream_t s, const char *who)
 {
@@ -1342,7 +1360,7 @@ int rdcnn_read(rdcnn_t h, float *u_dst, float *v_dst, int dst_is_host)
         e = hipMemcpyAsync(u_dst, s, bytes, hipMemcpyDeviceToHost, h->stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(v_dst, s + n, bytes, hipMemcpyDeviceToHost, h->stream);
-    } else if (rd::kernel_reads(n) && on_device_of(s, u_dst) && on_device_of(s, v_dst)) {
+    } else if (rd::kernel_reads((long long)n) && rd::kernel_may_read(s, (long long)n, u_dst, v_dst)) {
         e = rd::launch_copy_planes(s, (long long)n, u_dst, v_dst, h->stream);
     } else {  // also another device's memory, or the host's: the copies find their way
         e = hipMemcpyAsync(u_dst, s, bytes, hipMemcpyDeviceToDevice, h->stream);

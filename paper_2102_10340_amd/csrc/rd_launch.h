@@ -75,6 +75,7 @@ hipError_t launch_init(const float *x, float ka, float *state, long long n, hipS
 // The two planes of a state (n cells each) to u and v, on the device; whether that
 // is the faster read.
 bool kernel_reads(long long n);
+bool kernel_may_read(const float *src, long long n, const float *u, const float *v);
 hipError_t launch_copy_planes(const float *src, long long n, float *u, float *v, hipStream_t s);
 
 // One step, one thread per cell, neighbours read straight from global memory.
