@@ -116,8 +116,8 @@ bool tile_plan(int R, int C, int bc, int model, long long T, TilePlan *plan);
 // Cells up to which every run of six steps and more takes resident tiles, unless
 // the grid is narrow.
 constexpr long long kMidTileCells = 4300000;
-// Recording passes: the (even) depth of the passes of an n-step run, 0 if the
-// grid is for the streamed kernel; the shape of a pass of K steps.
+// Recording passes: the (even) depth of the passes of an n-step run, 0 if it
+// is for the streamed kernel; the shape of a pass of K steps.
 int tile_record_depth(int R, int C, long long n);
 TileShape tile_shape(int R, int C, int K);
 // Where a recording pass puts the states of its even levels: level j to at +
@@ -177,11 +177,8 @@ hipError_t launch_adjoint_pair(const AdjPlanes &io, const float *even_states, in
                                hipStream_t s);
 
 // The same on resident tiles (rd_tile_adj.h): the (even) depth of the passes
-// through S steps, 0 if the grid is for the streamed pairs; the shape of a pass
+// through S steps, 0 if they are for the streamed pairs; the shape of a pass
 // of K steps and the partial-sum slots it uses (one per wavefront of a tile).
-// Limit: us per reverse step, resident against streamed, 1024^2 2.81 / 3.95,
-// 1500^2 5.98 / 6.05.
-constexpr long long kMaxTileAdjCells = 2200000;
 int tile_adjoint_depth(int R, int C, long long S);
 TileShape tile_adjoint_shape(int R, int C, int K);
 long long tile_adjoint_slots(int R, int C, int K);

@@ -232,7 +232,9 @@ bool tile_plan(int R, int C, int bc, int model, long long T, TilePlan *plan)
 
 int tile_record_depth(int R, int C, long long n)
 {
-    if ((long long)R * C > 6000000 || n < 1) return 0;
+    // Speed-up of a run over the streamed recording: 8 steps 1.2 to 1.7 on 20 sizes of
+    // 256^2 to 2400^2, 50 steps 1.3 to 2.1; 6 steps 1.0 to 1.35; 2 steps 0.8 to 1.0.
+    if ((long long)R * C > 6000000 || !fills_tiles(R, C) || n < 6) return 0;
     return even_depth(table(R, C, false), n);
 }
 
@@ -240,7 +242,16 @@ TileShape tile_shape(int R, int C, int K) { return table(R, C, false).shape(K); 
 
 int tile_adjoint_depth(int R, int C, long long S)
 {
-    if ((long long)R * C > kMaxTileAdjCells || S < 2) return 0;
+    // The reverse tiles' workgroups fill a compute unit each, and lanes that hold a
+    // fold or a wrap (columns no multiple of 4) read the states column by column.
+    // Speed-up over the streamed pairs of 8 and of 50 steps, all sums: 512^2 1.61, 1.55;
+    // 1024^2 1.28, 1.28; 1100^2 1.32, 1.17; 1200^2 1.08, 1.01 (whole runs of 100 steps
+    // 0.88); 1300^2 1.00, 0.93; 1400^2 0.94, 0.90; other columns: 511^2 1.40, 1.39; 700x702
+    // 1.49, 1.44; 777x1001 1.15, 1.05 (10 steps 0.87); 1023x1025 0.86, 0.83; 1500x1002
+    // 0.74, 0.68.  Four steps: 512^2 1.22, 640x900 1.09, 900^2 0.77.
+    const long long n = (long long)R * C;
+    if (!fills_tiles(R, C) || n > (C % 4 == 0 ? 1250000 : 550000)) return 0;
+    if (S < (n <= 500000 ? 4 : 8)) return 0;
     return even_depth(table(R, C, true), S);
 }
 

@@ -100,3 +100,33 @@ def test_reads_by_one_kernel_up_to_their_size():
         assert reads(r * c), (r, c)
     for r, c in ((1500, 1500), (2048, 2048), (2600, 2665), (4096, 4096), (6000, 6000)):
         assert not reads(r * c), (r, c)
+
+
+record_depth = _lib.lib._ZN2rd17tile_record_depthEiix
+adjoint_depth = _lib.lib._ZN2rd18tile_adjoint_depthEiix
+for _f in (record_depth, adjoint_depth):
+    _f.argtypes, _f.restype = [ctypes.c_int, ctypes.c_int, ctypes.c_longlong], ctypes.c_int
+
+
+@pytest.mark.parametrize("R,C,S", [
+    (1200, 1200, 100), (1164, 1164, 8), (1300, 1300, 16), (1480, 1480, 400), (1333, 1401, 60),
+    (1023, 1025, 8), (1201, 1003, 150), (777, 1001, 10), (1500, 1002, 50), (1024, 1024, 4),
+    (900, 900, 2), (500000, 1, 8), (3, 100000, 50), (900, 1500, 20)])
+def test_reverse_passes_the_streamed_pairs_are_faster_at(R, C, S):
+    assert adjoint_depth(R, C, S) == 0
+
+
+@pytest.mark.parametrize("R,C,S", [(1, 1, 8), (256, 256, 100), (511, 511, 8), (700, 702, 50),
+                                   (1024, 1024, 8), (1024, 1024, 48), (1100, 1100, 400),
+                                   (512, 512, 4)])
+def test_reverse_passes_the_resident_tiles_are_faster_at(R, C, S):
+    d = adjoint_depth(R, C, S)
+    assert d >= 2 and d % 2 == 0
+
+
+def test_recordings_on_resident_tiles():
+    for R, C, n in ((1024, 1024, 2), (2200, 2200, 4), (2, 1000000, 50), (500000, 4, 8),
+                    (2500, 2500, 50)):
+        assert record_depth(R, C, n) == 0, (R, C, n)
+    for R, C, n in ((256, 256, 100), (1024, 1024, 8), (1333, 1401, 20), (2301, 2303, 50)):
+        assert record_depth(R, C, n) >= 6, (R, C, n)
