@@ -736,12 +736,15 @@ int rdcnn_batch_create(rdcnn_batch_t *out, int n, const int *rows, const int *co
     b->off.assign(offsets, offsets + n);
     b->g.resize(n);
     std::vector<rd::BatchInst> inst(n);
+    long long chunks = 0;
     for (int i = 0; i < n; ++i) {
         const rdcnn_params_t &p = params[i];
         rd::Gene g{p.dt, p.a, p.b, p.eps, p.c, p.k3, p.Du, p.Dv};
         b->g[i] = g;
         inst[i].off = offsets[i];
         inst[i].xoff = x_offsets[i];
+        inst[i].chunk0 = chunks;
+        chunks += ((long long)rows[i] * cols[i] + rd::kInitChunk - 1) / rd::kInitChunk;
         inst[i].R = rows[i];
         inst[i].C = cols[i];
         inst[i].g = g;
@@ -794,10 +797,8 @@ int rdcnn_batch_create(rdcnn_batch_t *out, int n, const int *rows, const int *co
         return bfail(RDCNN_ENOMEM, "rdcnn_batch_create: instance table: %s", hipGetErrorString(e));
     }
     e = hipMemcpy(b->insts_dev, inst.data(), sizeof(rd::BatchInst) * n, hipMemcpyHostToDevice);
-    long long most = 0;
-    for (int i = 0; i < n; ++i) most = std::max(most, (long long)rows[i] * cols[i]);
     if (e == hipSuccess)
-        e = rd::launch_batch_init(b->insts_dev, n, most, x_dev, ka, buf0_dev, b->stream);
+        e = rd::launch_batch_init(b->insts_dev, n, chunks, x_dev, ka, buf0_dev, b->stream);
     if (e != hipSuccess) {
         (void)hipFree(b->insts_dev);
         delete b;

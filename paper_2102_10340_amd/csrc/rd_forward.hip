@@ -47,38 +47,46 @@ hipError_t launch_init(const float *x, float ka, float *state, long long n, hipS
     return hipGetLastError();
 }
 
-// One workgroup per kInitChunk cells of one instance (a batch of small grids is
-// bound by launches: 256 of them took 2.2 us each plus their host time, one
-// launch over all 10 us).
-constexpr int kInitChunk = 8192;
-
+// One workgroup per kInitChunk cells of one instance, found from its number by
+// bisection (a batch of small grids is bound by launches: 256 of them took 2.2 us
+// each plus their host time, one launch over all 10 us; with the largest instance's
+// workgroups for each, one 4096^2 among 1000 of 64^2 took 3.7 ms to create, 1.9 this
+// way).
 __global__ __launch_bounds__(256) void batch_init_kernel(const BatchInst *__restrict__ insts,
-                                                         int chunks, const float *__restrict__ x,
-                                                         float ka, float *__restrict__ state)
+                                                         int n, long long first,
+                                                         const float *__restrict__ x, float ka,
+                                                         float *__restrict__ state)
 {
-    const int i = blockIdx.x / chunks, q = blockIdx.x - i * chunks;
-    const BatchInst I = insts[i];
-    const long long n = (long long)I.R * I.C, k0 = (long long)q * kInitChunk;
-    const long long k1 = k0 + kInitChunk < n ? k0 + kInitChunk : n;
+    const long long id = first + blockIdx.x;
+    int lo = 0, hi = n;  // the last instance whose first workgroup is not past id
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (insts[mid].chunk0 <= id)
+            lo = mid;
+        else
+            hi = mid;
+    }
+    const BatchInst I = insts[lo];
+    const long long cells = (long long)I.R * I.C, k0 = (id - I.chunk0) * kInitChunk;
+    const long long k1 = k0 + kInitChunk < cells ? k0 + kInitChunk : cells;
     const float *xi = x + I.xoff;
     float *si = state + I.off;
     for (long long k = k0 + threadIdx.x; k < k1; k += 256) {
         const float u = ka * xi[k];
         si[k] = u;
-        si[n + k] = u;
+        si[cells + k] = u;
     }
 }
 
-hipError_t launch_batch_init(const BatchInst *insts, int n, long long max_cells, const float *x,
+hipError_t launch_batch_init(const BatchInst *insts, int n, long long chunks, const float *x,
                              float ka, float *state, hipStream_t s)
 {
-    const long long chunks = (max_cells + kInitChunk - 1) / kInitChunk;
-    // grids of up to 2^30 workgroups; more instances go in slices
-    const long long most = chunks < (1LL << 30) ? (1LL << 30) / chunks : 1;
-    for (long long i = 0; i < n; i += most) {
-        const long long m = n - i < most ? n - i : most;
-        hipLaunchKernelGGL(batch_init_kernel, dim3((unsigned)(m * chunks)), dim3(256), 0, s,
-                           insts + i, (int)chunks, x, ka, state);
+    // a launch may have fewer than 2^32 threads
+    constexpr long long kMost = 1 << 23;
+    for (long long first = 0; first < chunks; first += kMost) {
+        const long long m = chunks - first < kMost ? chunks - first : kMost;
+        hipLaunchKernelGGL(batch_init_kernel, dim3((unsigned)m), dim3(256), 0, s, insts, n, first, x,
+                           ka, state);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -206,6 +206,7 @@ hipError_t launch_adjoint_finish(const double *partial, int ntiles, const Gene &
 struct BatchInst {
     long long off;   // float offset of the instance in a packed buffer
     long long xoff;  // float offset of its initial image
+    long long chunk0;  // its first workgroup in launch_batch_init
     int R, C;
     Gene g;
 };
@@ -257,9 +258,10 @@ hipError_t launch_batch_whole(const BatchInst *insts, const WholeInst *list, int
                               int waves, const float *in, float *out, int bc, long long T,
                               hipStream_t s);
 
-// u = v = ka * x for every instance of a batch, in one launch; max_cells: cells of
-// the largest instance.
-hipError_t launch_batch_init(const BatchInst *insts, int n, long long max_cells, const float *x,
+// u = v = ka * x for every instance of a batch, in one launch of `chunks` workgroups:
+// one per kInitChunk cells of each instance.
+constexpr int kInitChunk = 8192;
+hipError_t launch_batch_init(const BatchInst *insts, int n, long long chunks, const float *x,
                              float ka, float *state, hipStream_t s);
 
 // Per-instance atlas statistics: chunks of at most kStatChunk cells, one
