@@ -51,26 +51,32 @@ __device__ void add_grads(const double *S, const Gene &g, unsigned mask, double 
     for (int q = 0; q < 8; ++q) dtheta[q] = (mask >> q) & 1u ? dtheta[q] + d[q] : __builtin_nan("");
 }
 
-// One thread per instance: sum the partials of its tiles (tile ids
-// tiles_of[first[i] .. first[i+1]), ascending) and add its gradients to
-// dtheta[8 i ..].
+// One wavefront per instance: sum the partials of its tiles (tile ids
+// tiles_of[first[i] .. first[i+1]), ascending: lane l takes every 64th, then the
+// lanes fold pairwise) and add its gradients to dtheta[8 i ..].  A thread alone took
+// 0.14 us a tile, 0.2 ms for a 1024^2 instance cut into 16-row tiles.
 __global__ __launch_bounds__(256) void batch_adjoint_finish_kernel(const double *partial,
                                                                    const int *first,
                                                                    const int *tiles_of,
                                                                    const BatchInst *insts, int n,
                                                                    unsigned mask, double *dtheta)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    double S[NSUM];
+    const int lane = threadIdx.x & 63;
+    for (int i = blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += gridDim.x * 4) {
+        double S[NSUM];
 #pragma unroll
-    for (int k = 0; k < NSUM; ++k) S[k] = 0.0;
-    for (int q = first[i]; q < first[i + 1]; ++q) {
-        const double *p = partial + (size_t)tiles_of[q] * NSUM;
+        for (int k = 0; k < NSUM; ++k) S[k] = 0.0;
+        for (int q = first[i] + lane; q < first[i + 1]; q += 64) {
+            const double *p = partial + (size_t)tiles_of[q] * NSUM;
 #pragma unroll
-        for (int k = 0; k < NSUM; ++k) S[k] += p[k];
+            for (int k = 0; k < NSUM; ++k) S[k] += p[k];
+        }
+#pragma unroll
+        for (int k = 0; k < NSUM; ++k)
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) S[k] += __shfl_xor(S[k], off, 64);
+        if (lane == 0) add_grads(S, insts[i].g, mask, dtheta + 8 * (size_t)i);
     }
-    add_grads(S, insts[i].g, mask, dtheta + 8 * (size_t)i);
 }
 
 // Shared parameters: dtheta[q] += sum over instances i = 0 .. n-1, in that
@@ -208,8 +214,9 @@ hipError_t launch_batch_adjoint_finish(const double *partial, const int *first, 
                                        const BatchInst *insts, int n, unsigned mask,
                                        double *dtheta, hipStream_t s)
 {
-    hipLaunchKernelGGL(batch_adjoint_finish_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                       s, partial, first, tiles_of, insts, n, mask, dtheta);
+    const int blocks = n < 4 * 65536 ? (n + 3) / 4 : 65536;
+    hipLaunchKernelGGL(batch_adjoint_finish_kernel, dim3((unsigned)blocks), dim3(256), 0, s, partial,
+                       first, tiles_of, insts, n, mask, dtheta);
     return hipGetLastError();
 }
 
