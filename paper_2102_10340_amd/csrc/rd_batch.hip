@@ -378,14 +378,14 @@ std::map<std::pair<int, int>, int> size_classes(const rdcnn_batch *b, bool skip_
     return n;
 }
 
-// Tiles of kTallRows rows that K-step passes cut the sizes into.
+// Tiles of `rows` rows that K-step passes cut the sizes into.
 constexpr int kTallRows = 128;
-long long tall_tiles(const std::map<std::pair<int, int>, int> &sizes, int cpl, int K)
+long long tiles_in(const std::map<std::pair<int, int>, int> &sizes, int cpl, int K, int rows)
 {
     const int wout = 64 * cpl - 2 * ((K + cpl - 1) / cpl * cpl);
     long long n = 0;
     for (const auto &z : sizes)
-        n += (long long)z.second * ((z.first.first + kTallRows - 1) / kTallRows) *
+        n += (long long)z.second * ((z.first.first + rows - 1) / rows) *
              ((z.first.second + wout - 1) / wout);
     return n;
 }
@@ -454,7 +454,7 @@ void batch_config(rdcnn_batch *b, int *cpl, int *depth, int *seg)
         b->auto_cpl = 2;
         b->auto_depth = 12;
         b->auto_seg = kTallRows;
-        if (tall_tiles(sizes, 2, 12) < 1536) {
+        if (tiles_in(sizes, 2, 12, kTallRows) < 1536) {
             b->auto_depth = kCutDepth;
             best_cut(sizes, kStepCost, 1, 2, {8, 12, 16, 24, 32, 48, 64, 96, 128}, &b->auto_cpl,
                      &b->auto_seg);
@@ -591,7 +591,7 @@ int setup_adj(rdcnn_batch *b)
         // with them, 65.2 with the cheapest cut's 64 rows)
         const auto sizes = size_classes(b, false);
         seg = kTallRows;
-        if (tall_tiles(sizes, cpl, b->adj_depth) < 2048)
+        if (tiles_in(sizes, cpl, b->adj_depth, kTallRows) < 2048)
             best_cut(sizes, kAdjCost, cpl, cpl, {16, 32, 64, 128}, &cpl, &seg);
     }
     int rc = build_tiles(b, cpl, b->adj_depth, seg, false, tiles);
@@ -854,12 +854,20 @@ int batch_record(rdcnn_batch *b, long long T, float *traj, bool even, const char
     // plain pass's led sweeps on 64 x 1024^2 (full: 64 rows; even-time: 32 rows,
     // 0.57 Tcell-steps/s against 0.50 at 64); smaller batches take less where
     // that fills the chip (6 of 500 x 640, even-time: 31 us a pass against 40).
+    // Full recording, whose stores lead, stays at 64 rows from 1152 such tiles on
+    // (8 steps, us, 64 rows / the cheapest cut: two of 2048^2 243 / 262, 3000^2
+    // 256 / 271; four of 1024^2, 640 tiles, 155 / 106).
     if (!b->depth) {
         int *cut = b->rec_cut[even ? 1 : 0];
-        if (!cut[0] && even)
-            best_cut(size_classes(b, false), kStepCost, 1, 2, {8, 16, 32}, &cut[0], &cut[1]);
-        else if (!cut[0])
-            best_cut(size_classes(b, false), kStepCost, 1, 2, {8, 16, 32, 64}, &cut[0], &cut[1]);
+        if (!cut[0]) {
+            const auto sizes = size_classes(b, false);
+            cut[0] = 2;
+            cut[1] = 64;
+            if (even)
+                best_cut(sizes, kStepCost, 1, 2, {8, 16, 32}, &cut[0], &cut[1]);
+            else if (tiles_in(sizes, 2, 8, 64) < 1152)
+                best_cut(sizes, kStepCost, 1, 2, {8, 16, 32, 64}, &cut[0], &cut[1]);
+        }
         cpl = cut[0];
         seg = cut[1];
     } else if (!b->seg_rows) {
