@@ -514,8 +514,8 @@ int rdcnn_batch_step_record(rdcnn_batch_t b, long long T, float *traj);
 /*
  * rdcnn_batch_set_adjoint_kernel -- pass shape of rdcnn_batch_adjoint: depth
  * (reverse steps per pass: 1, 2, 4 or 8), cols_per_lane (1 or 2), seg_rows
- * (rows per tile); 0 stands for (8, 1, 128).  Without this call the rows per
- * tile follow the batch's size.  Passes are made shallower
+ * (rows per tile); 0 keeps the default: 8, 1 and rows that follow the batch's
+ * size.  Passes are made shallower
  * where one instance's span of a pass's states would pass 4 GiB.  Errors:
  * RDCNN_EINVAL.
  */

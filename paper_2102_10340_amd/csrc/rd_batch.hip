@@ -946,13 +946,12 @@ int rdcnn_batch_set_adjoint_kernel(rdcnn_batch_t b, int depth, int cols_per_lane
     if (!b) return bfail(RDCNN_EINVAL, "rdcnn_batch_set_adjoint_kernel: NULL handle");
     if (depth == 0) depth = 8;
     if (cols_per_lane == 0) cols_per_lane = 1;
-    if (seg_rows == 0) seg_rows = 128;
     if (depth != 1 && depth != 2 && depth != 4 && depth != 8)
         return bfail(RDCNN_EINVAL, "rdcnn_batch_set_adjoint_kernel: depth %d not in {1,2,4,8}", depth);
     if (cols_per_lane != 1 && cols_per_lane != 2)
         return bfail(RDCNN_EINVAL, "rdcnn_batch_set_adjoint_kernel: cols_per_lane %d not in {1,2}",
                      cols_per_lane);
-    if (seg_rows < 1) return bfail(RDCNN_EINVAL, "rdcnn_batch_set_adjoint_kernel: seg_rows < 1");
+    if (seg_rows < 0) return bfail(RDCNN_EINVAL, "rdcnn_batch_set_adjoint_kernel: seg_rows < 0");
     free_adj(b);
     b->adj_depth = depth;
     b->adj_cpl = cols_per_lane;
