@@ -187,7 +187,9 @@ int rdcnn_current(rdcnn_t h, float **state_dev);
  *   kernel); 2: register-streamed kernel doing up to `depth` steps per HBM pass,
  *   for every call that steps (the recording calls cap it to what they support);
  *   3: as 2 for rdcnn_step and rdcnn_step_checkpoints only, the recording calls
- *   keep their automatic shapes (what an autotuned forward shape wants).
+ *   keep their automatic shapes (what an autotuned forward shape wants);
+ *   4: a shape rdcnn_pass_config reported for resident tiles, as kind 0 (their
+ *   shapes follow the steps of each run).
  *   cols_per_lane 1 or 2 (depth 1..16) or 4 (depth 1..12); seg_rows: output rows
  *   per wavefront, 0 = automatic.  Other fields are ignored for kinds 0 and 1.
  *   Every setting gives bit-identical states.  Errors: RDCNN_EINVAL.
@@ -196,11 +198,12 @@ int rdcnn_set_kernel(rdcnn_t h, int kind, int depth, int cols_per_lane, int seg_
 
 /*
  * rdcnn_pass_config -- the pass shape later rdcnn_step calls use, with the
- * automatic choices resolved: *kind 1 (one thread per cell), 2 (streamed) or 4
- * (resident tiles, the automatic choice up to 6 million cells, 4.5 on most
- * tori, 32 for the CNN; not a kind rdcnn_set_kernel takes), *depth steps per
- * pass (kind 4: of a long run; other runs are cut evenly), *cols_per_lane,
- * *seg_rows output rows per wavefront (kind 4: per workgroup)
+ * automatic choices resolved for a long run: *kind 1 (one thread per cell), 2
+ * (streamed) or 4 (resident tiles, the automatic choice up to 4 million cells
+ * unless the grid is a few cells wide, and on some grids up to 6, 20 for the
+ * CNN; shorter runs are cut evenly, runs of a few steps are streamed), *depth
+ * steps per pass, *cols_per_lane, *seg_rows output rows per wavefront (kind 4:
+ * per workgroup)
  * (the paper's block/grid choice, Sec. II.B, made explicit).  Host-only, no
  * device work.  Errors: RDCNN_EINVAL (NULL argument).
  */

@@ -1419,6 +1419,16 @@ int rdcnn_set_kernel(rdcnn_t h, int kind, int depth, int cols_per_lane, int seg_
         h->kind = kind;
         return RDCNN_OK;
     }
+    if (kind == 4) {
+        // what rdcnn_pass_config reports of automatic resident tiles, whose shape
+        // follows each run's steps
+        if (depth < 1 || depth > rd::kMaxTileDepth || (cols_per_lane != 2 && cols_per_lane != 4) ||
+            seg_rows < 1)
+            return fail(RDCNN_EINVAL, "rdcnn_set_kernel: no resident tiles of depth %d, "
+                        "cols_per_lane %d, %d rows", depth, cols_per_lane, seg_rows);
+        h->kind = 0;
+        return RDCNN_OK;
+    }
     if (kind != 2 && kind != 3) return fail(RDCNN_EINVAL, "rdcnn_set_kernel: unknown kind %d", kind);
     if (cols_per_lane != 1 && cols_per_lane != 2 && cols_per_lane != 4)
         return fail(RDCNN_EINVAL, "rdcnn_set_kernel: cols_per_lane %d not in {1,2,4}", cols_per_lane);

@@ -243,8 +243,9 @@ class Simulation:
                    seg_rows: int = 0) -> None:
         """0 automatic, 1 one-thread-per-cell reference kernel, 2 streamed kernel
         with `depth` steps per pass, 3 the same for plain steps only (the
-        recording calls keep their automatic shapes); bit-identical results
-        for every choice."""
+        recording calls keep their automatic shapes), 4 a shape pass_config
+        reported for resident tiles (as 0); bit-identical results for every
+        choice."""
         check(lib.rdcnn_set_kernel(self._h, int(kind), int(depth), int(cols_per_lane),
                                    int(seg_rows)))
         self._kernel = (int(kind), int(depth), int(cols_per_lane), int(seg_rows))

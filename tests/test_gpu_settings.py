@@ -33,3 +33,26 @@ def test_batch_adjoint_default_rows():
     b.set_adjoint_kernel()
     assert np.array_equal(dtheta(), want)
     b.close()
+
+
+@pytest.mark.parametrize("shape", [(128, 128), (777, 1301), (2500, 2500), (3000, 100)],
+                         ids=lambda s: "%dx%d" % s)
+def test_reported_pass_shape_can_be_set(shape):
+    """set_kernel takes what pass_config reports, on this grid and on another, and
+    steps go on as before."""
+    from paper_2102_10340_amd import Simulation
+    from paper_2102_10340_amd._lib import RDCNNError
+    x = torch.from_numpy(W.uniform_x(*shape, 3)).cuda()
+    a, b, other = (Simulation(t, W.PLAIN_GENE, tuned=False) for t in (x, x, x[:64, :64].contiguous()))
+    cfg = a.pass_config()
+    a.set_kernel(**cfg)
+    assert a.pass_config() == cfg
+    other.set_kernel(**cfg)
+    other.step(9)
+    for T in (3, 17):
+        assert torch.equal(a.step(T).state(), b.step(T).state())
+    for bad in ((4, 0, 4, 8), (4, 17, 4, 8), (4, 8, 1, 8), (4, 8, 4, 0), (5, 8, 4, 8)):
+        with pytest.raises(RDCNNError):
+            a.set_kernel(*bad)
+    for s in (a, b, other):
+        s.close()
