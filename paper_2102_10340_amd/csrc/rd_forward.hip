@@ -50,7 +50,7 @@ hipError_t launch_init(const float *x, float ka, float *state, long long n, hipS
 // One workgroup per kInitChunk cells of one instance, found from its number by
 // bisection (a batch of small grids is bound by launches: 256 of them took 2.2 us
 // each plus their host time, one launch over all 10 us; with the largest instance's
-// workgroups for each, one 4096^2 among 1000 of 64^2 took 3.7 ms to create, 1.9 this
+// workgroups for each, one 4096^2 among 1000 of 64^2 took 3.7 ms to create, 3.2 this
 // way).
 __global__ __launch_bounds__(256) void batch_init_kernel(const BatchInst *__restrict__ insts,
                                                          int n, long long first,

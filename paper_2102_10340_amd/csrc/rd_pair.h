@@ -10,14 +10,16 @@
 // level an iteration.  That leaves the K rows at the far end: of a 35-row walk
 // a wavefront computes 1.11 times its cells instead of 1.22.
 //
-// What bounds it: the walk of one wavefront.  Two wavefronts a SIMD (226 VGPRs)
-// each issue a vector instruction every four cycles at best, 28 % of their time
-// goes to waits, and the clock falls to 2.0 GHz under this load.  East and west
+// What bounds it: the walk of one wavefront.  Two wavefronts a SIMD (221 VGPRs, 7
+// spilled SGPRs) each issue a vector instruction every four cycles at best, 17 to
+// 20 % of their time goes to waits, and the clock falls to 2.0 GHz under this load.  East and west
 // neighbours come by ds_bpermute, asked for one level ahead and held there by a
 // scheduling barrier: DPP operands stop two wavefronts' instructions from
 // issuing side by side.  4096^2, 8 steps a pass, one GPU: 95.3 us a pass alone
 // with DPP; pairs 91 with DPP, 88 with ds_bpermute, 85 with the level-0 window
-// of three rows (fetched one iteration ahead) and the barrier.  Three rows a
+// of three rows (fetched one iteration ahead) and the barrier, 75 with strips that
+// end at the sides (random state; 72 on the slow-growth run's mostly quiet one).
+// Three rows a
 // level and K = 8 fill the registers; K = 6 at three wavefronts a SIMD took 2 %
 // more per step, four wavefronts a workgroup 12 % more.
 #pragma once
@@ -175,7 +177,7 @@ __device__ __forceinline__ void pair_body(const StreamArgsT<M> &A, const Tile<CP
     }
 }
 
-// Tiles of A.t: every one takes vectors (pair_geometry).
+// Tiles of A.t: every one takes vectors (pair_pass, plain_geometry).
 template <class M, int CPL, int K>
 __global__ __launch_bounds__(128) void pair_step_kernel(StreamArgsT<M> A)
 {

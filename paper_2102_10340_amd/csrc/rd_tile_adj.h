@@ -11,10 +11,11 @@
 // pair; each wavefront adds its total to a slot of its own, so the sums have a
 // fixed order.
 //
-// What bounds it: at two wavefronts per SIMD (242 VGPRs for 4 columns x 4 rows)
-// the latency of a step, then the reads of E.  us per reverse step on grids that
-// the streamed pairs walk at 2.17 / 2.27 / 2.59 / 3.95 / 6.05: 128^2 1.08, 256^2
-// 1.11, 512^2 1.56, 1024^2 2.81, 1500^2 5.98.
+// What bounds it: at two wavefronts per SIMD (4 columns x 4 rows take all 256 VGPRs
+// and spill 14, with the lam-weighted sums 22: 60 and 92 bytes a lane) the latency of
+// a step, then the reads of E.  A workgroup of 8 such wavefronts fills a compute unit.
+// us per reverse step on grids that the streamed pairs walk at 2.17 / 2.27 / 2.59 /
+// 3.95: 128^2 1.08, 256^2 1.11, 512^2 1.56, 1024^2 2.81.
 #pragma once
 #include "rd_adj_body.h"
 #include "rd_tile_body.h"

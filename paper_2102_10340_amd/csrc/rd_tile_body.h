@@ -19,7 +19,9 @@
 // (one per 2.3-2.9 cycles measured, against 4.1-4.3 in code that holds a DPP
 // shift even once in 32 instructions), and a swizzle costs about 7.  LDS writes
 // are the slow side of LDS here (78 bytes per clock against 200-250 read), which
-// is why only the two outer rows of a block are written.  Measured per step,
+// is why only the two outer rows of a block are written.  The largest block (4
+// columns x 6 rows) takes all 128 VGPRs of its 1024-thread bound and spills 7 (24
+// bytes a lane).  Measured per step,
 // against the streamed kernel at its tuned shape: 128^2 0.54 us (1.17), 256^2
 // 0.55 (1.23), 512^2 0.75 (1.57), 1024^2 1.39 (2.26), 2048^2 3.33 (4.2).
 #pragma once
