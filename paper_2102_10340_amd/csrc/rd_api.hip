@@ -1360,7 +1360,7 @@ int rdcnn_read(rdcnn_t h, float *u_dst, float *v_dst, int dst_is_host)
         e = hipMemcpyAsync(u_dst, s, bytes, hipMemcpyDeviceToHost, h->stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(v_dst, s + n, bytes, hipMemcpyDeviceToHost, h->stream);
-    } else if (rd::kernel_reads((long long)n) && rd::kernel_may_read(s, (long long)n, u_dst, v_dst)) {
+    } else if (rd::kernel_may_read(s, (long long)n, u_dst, v_dst)) {
         e = rd::launch_copy_planes(s, (long long)n, u_dst, v_dst, h->stream);
     } else {  // also another device's memory, or the host's: the copies find their way
         e = hipMemcpyAsync(u_dst, s, bytes, hipMemcpyDeviceToDevice, h->stream);

@@ -126,42 +126,46 @@ hipError_t launch_count_nonfinite(const float *x, long long n, int *count, hipSt
 // 128^2 grid took 2 x 2.0 us of GPU time and two submissions (about 2.8 us of
 // host time each), one launch 2.2 us.  vec: every pointer is 16-byte aligned and
 // n a multiple of 4.
+//
+// Bound by memory.  Stores pass the caches by: a read's copy is not what the next
+// pass reads (4096^2, a step and a read: 129 us with plain stores, 90 so, 135 with
+// copies; the same up to 3100x3333).  At most kReadBlocks workgroups: after a launch of more than 8192
+// wavefronts a streamed pass, two wavefronts of which fill a SIMD, ran up to a third
+// slower than after fewer (steps and a read, us, 16384 or 3072 workgroups / 2048
+// / copies: 2048^2, 5 steps, 38.0 / 32.9 / 34.1; 2600x2665, 8, 76.8 / 63.8 / 64.3; the
+// CNN on 4096^2, 8, 230 / 177 / 195).
+constexpr int kReadBlocks = 2048;
+
 __global__ __launch_bounds__(256) void copy_planes_kernel(const float *__restrict__ src, long long n,
                                                           float *__restrict__ u,
                                                           float *__restrict__ v, int vec)
 {
+    using f4 = float __attribute__((ext_vector_type(4)));
     const long long stride = (long long)gridDim.x * blockDim.x;
     const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (vec) {
-        const float4 *su = reinterpret_cast<const float4 *>(src);
-        const float4 *sv = reinterpret_cast<const float4 *>(src + n);
-        float4 *du = reinterpret_cast<float4 *>(u), *dv = reinterpret_cast<float4 *>(v);
+        const f4 *su = reinterpret_cast<const f4 *>(src);
+        const f4 *sv = reinterpret_cast<const f4 *>(src + n);
+        f4 *du = reinterpret_cast<f4 *>(u), *dv = reinterpret_cast<f4 *>(v);
         for (long long i = t; i < n / 4; i += stride) {
-            const float4 a = su[i], b = sv[i];
-            du[i] = a;
-            dv[i] = b;
+            const f4 a = su[i], b = sv[i];
+            __builtin_nontemporal_store(a, du + i);
+            __builtin_nontemporal_store(b, dv + i);
         }
     } else {
         for (long long i = t; i < n; i += stride) {
             const float a = src[i], b = src[n + i];
-            u[i] = a;
-            v[i] = b;
+            __builtin_nontemporal_store(a, u + i);
+            __builtin_nontemporal_store(b, v + i);
         }
     }
 }
-
-// Whether one kernel reads both planes of n cells: where the two submissions of the
-// copies are what a read takes.  Beyond, the copies are as fast, and after the
-// kernel the next streamed pass is up to a fifth slower (steps and a read, kernel /
-// copies, us: 128^2, 8 steps, 11.6 / 17.4; 1024x1536, 8, 20.8 / 22.0; 1500^2, 5, 24.5 /
-// 23.4; 2600x2665, 8, 77 / 64; 4096^2, 8, 129 / 139, but the CNN's 233 / 194).
-bool kernel_reads(long long n) { return n <= 1600000; }
 
 hipError_t launch_copy_planes(const float *src, long long n, float *u, float *v, hipStream_t s)
 {
     const int vec = n % 4 == 0 && ((uintptr_t)src | (uintptr_t)u | (uintptr_t)v) % 16 == 0;
     long long blocks = ((vec ? n / 4 : n) + 255) / 256;
-    if (blocks > 16384) blocks = 16384;
+    if (blocks > kReadBlocks) blocks = kReadBlocks;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(copy_planes_kernel, dim3((unsigned)blocks), dim3(256), 0, s, src, n, u, v, vec);
     return hipGetLastError();

@@ -72,9 +72,8 @@ TileArgs tile_args(int R, int C, int bc, const StreamGeom &geom);
 // u = v = ka * x over n cells (state holds u then v).
 hipError_t launch_init(const float *x, float ka, float *state, long long n, hipStream_t s);
 
-// The two planes of a state (n cells each) to u and v, on the device; whether that
-// is the faster read.
-bool kernel_reads(long long n);
+// The two planes of a state (n cells each) to u and v, on the device, and whether it
+// may take the place of two copies.
 bool kernel_may_read(const float *src, long long n, const float *u, const float *v);
 hipError_t launch_copy_planes(const float *src, long long n, float *u, float *v, hipStream_t s);
 

@@ -72,3 +72,22 @@ def test_reads_over_the_state_and_each_other_are_as_two_copies():
     got = bytes_[2:8 * n + 2].clone().view(torch.float32)
     assert torch.equal(got[:n].view(R, C), want_u) and torch.equal(got[n:].view(R, C), want_v)
     sim.close()
+
+
+@pytest.mark.parametrize("shape", [(1, 1), (3, 5), (64, 64), (513, 1023), (1025, 2048), (1449, 1449)])
+@pytest.mark.parametrize("offset", [0, 1])  # offset in floats from a vector's address
+def test_one_launch_reads_every_size(shape, offset):
+    """One cell to several trips of the kernel's grid, vectors and single floats."""
+    from paper_2102_10340_amd import Simulation
+    from paper_2102_10340_amd._lib import check, lib
+    n = shape[0] * shape[1]
+    sim = Simulation(torch.from_numpy(W.uniform_x(*shape, 3)).cuda(), W.PLAIN_GENE, tuned=False)
+    sim.step(1)
+    out = torch.full((2 * n + offset + 4,), -7.0, device="cuda")
+    u = out.data_ptr() + 4 * offset
+    check(lib.rdcnn_read(sim._h, u, u + 4 * n, 0))
+    st = sim.state()
+    assert torch.equal(out[offset:offset + n].view(shape), st[0])
+    assert torch.equal(out[offset + n:offset + 2 * n].view(shape), st[1])
+    assert bool((out[:offset] == -7).all()) and bool((out[offset + 2 * n:] == -7).all())
+    sim.close()

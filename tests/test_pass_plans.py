@@ -91,17 +91,6 @@ def test_runs_the_resident_tiles_are_faster_at(R, C, T, model, bc):
     assert p.deeper == 0 or p.deep.K == p.base.K + 1
 
 
-def test_reads_by_one_kernel_up_to_their_size():
-    """One launch reads small states; beyond, copies do (after the kernel the next
-    streamed pass was up to a fifth slower)."""
-    reads = _lib.lib._ZN2rd12kernel_readsEx
-    reads.argtypes, reads.restype = [ctypes.c_longlong], ctypes.c_bool
-    for r, c in ((1, 1), (128, 128), (777, 1301), (1024, 1024)):
-        assert reads(r * c), (r, c)
-    for r, c in ((1500, 1500), (2048, 2048), (2600, 2665), (4096, 4096), (6000, 6000)):
-        assert not reads(r * c), (r, c)
-
-
 record_depth = _lib.lib._ZN2rd17tile_record_depthEiix
 adjoint_depth = _lib.lib._ZN2rd18tile_adjoint_depthEiix
 for _f in (record_depth, adjoint_depth):
