@@ -948,7 +948,8 @@ struct PairPlan {
     long long need;  // partial-sum slots of the widest tiling
 };
 
-int plan_pairs(const rdcnn_sim *h, long long S, int every, const char *who, PairPlan *pl)
+int plan_pairs(const rdcnn_sim *h, long long S, int every, const char *who, PairPlan *pl,
+               bool chain = false)
 {
     int cpl = h->adj_cpl, depth = h->adj_depth, seg = h->adj_seg_rows;
     if (depth == 0) adj_even_auto_config(h, &cpl, &depth, &seg);
@@ -968,7 +969,7 @@ int plan_pairs(const rdcnn_sim *h, long long S, int every, const char *who, Pair
     // An odd S starts with one plain reverse step (state s_{S-1} is even);
     // then paired passes of `depth` steps and one shorter even remainder.
     const long long even = S & ~1LL;
-    int tile_depth = h->adj_depth == 0 ? rd::tile_adjoint_depth(h->R, h->C, even) : 0;
+    int tile_depth = h->adj_depth == 0 ? rd::tile_adjoint_depth(h->R, h->C, even, chain) : 0;
     auto first_of = [&](int d) { return (int)(even < d ? even : d); };
     auto last_of = [&](int d) { return even == 0 ? 0 : (int)(even % d == 0 ? d : even % d); };
     long long need = 0;
@@ -1271,8 +1272,8 @@ int rdcnn_step_bwd_ckpt(rdcnn_t h, const float *ckpt_dev, long long T, long long
     // One partial buffer for every segment: cleared once, folded once.
     const long long Llast = T - (nseg - 1) * S;
     PairPlan pl, plast;
-    int rc = plan_pairs(h, Smax, 2, who, &pl);
-    if (rc == RDCNN_OK) rc = plan_pairs(h, Llast, 2, who, &plast);
+    int rc = plan_pairs(h, Smax, 2, who, &pl, true);
+    if (rc == RDCNN_OK) rc = plan_pairs(h, Llast, 2, who, &plast, true);
     if (rc != RDCNN_OK) return rc;
     const long long need = pl.need > plast.need ? pl.need : plast.need;
     if ((rc = ensure_partial(h, need, who)) != RDCNN_OK) return rc;
@@ -1318,7 +1319,7 @@ int rdcnn_step_bwd_ckpt(rdcnn_t h, const float *ckpt_dev, long long T, long long
         // Reverse passes of segment k on the handle's stream, overlapping the
         // recompute of segment k-1.
         PairPlan plk;
-        if ((rc = plan_pairs(h, L, 2, who, &plk)) != RDCNN_OK) return rc;
+        if ((rc = plan_pairs(h, L, 2, who, &plk, true)) != RDCNN_OK) return rc;
         rc = run_pairs(h, traj, 2, L, pp, plk, h->partial, dtheta_accum, who, false);
         if (rc != RDCNN_OK) return rc;
         if ((e = hipEventRecord(done[b], h->stream)) != hipSuccess) return hip_fail(e, who);

@@ -129,11 +129,11 @@ hipError_t launch_count_nonfinite(const float *x, long long n, int *count, hipSt
 //
 // Bound by memory.  Stores pass the caches by: a read's copy is not what the next
 // pass reads (4096^2, a step and a read: 129 us with plain stores, 90 so, 135 with
-// copies; the same up to 3100x3333).  At most kReadBlocks workgroups: after a launch of more than 8192
-// wavefronts a streamed pass, two wavefronts of which fill a SIMD, ran up to a third
-// slower than after fewer (steps and a read, us, 16384 or 3072 workgroups / 2048
-// / copies: 2048^2, 5 steps, 38.0 / 32.9 / 34.1; 2600x2665, 8, 76.8 / 63.8 / 64.3; the
-// CNN on 4096^2, 8, 230 / 177 / 195).
+// copies; the same up to 3100x3333).  At most kReadBlocks workgroups: after a launch
+// of more than 8192 wavefronts a streamed pass, two wavefronts of which fill a SIMD,
+// ran up to a third slower than after fewer (steps and a read, us, 16384 or 3072
+// workgroups / 2048 / copies: 2048^2, 5 steps, 38.0 / 32.9 / 34.1; 2600x2665, 8, 76.8 /
+// 63.8 / 64.3; the CNN on 4096^2, 8, 230 / 177 / 195).
 constexpr int kReadBlocks = 2048;
 
 __global__ __launch_bounds__(256) void copy_planes_kernel(const float *__restrict__ src, long long n,

@@ -176,9 +176,10 @@ hipError_t launch_adjoint_pair(const AdjPlanes &io, const float *even_states, in
                                hipStream_t s);
 
 // The same on resident tiles (rd_tile_adj.h): the (even) depth of the passes
-// through S steps, 0 if they are for the streamed pairs; the shape of a pass
-// of K steps and the partial-sum slots it uses (one per wavefront of a tile).
-int tile_adjoint_depth(int R, int C, long long S);
+// through S steps, 0 if they are for the streamed pairs (chain: of one recorded
+// segment of several, whose reverse passes overlap the next one's recording); the
+// shape of a pass of K steps and the partial-sum slots it uses (one per wavefront of a tile).
+int tile_adjoint_depth(int R, int C, long long S, bool chain);
 TileShape tile_adjoint_shape(int R, int C, int K);
 long long tile_adjoint_slots(int R, int C, int K);
 hipError_t launch_tile_adjoint(const AdjPlanes &io, const float *even_states, int every,

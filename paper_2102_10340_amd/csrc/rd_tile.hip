@@ -242,19 +242,27 @@ int tile_record_depth(int R, int C, long long n)
 
 TileShape tile_shape(int R, int C, int K) { return table(R, C, false).shape(K); }
 
-int tile_adjoint_depth(int R, int C, long long S)
+int tile_adjoint_depth(int R, int C, long long S, bool chain)
 {
-    // The reverse tiles' workgroups fill a compute unit each, and lanes that hold a
-    // fold or a wrap (columns no multiple of 4) read the states column by column.
-    // Speed-up over the streamed pairs of 8 and of 50 steps, all sums: 512^2 1.61, 1.55;
-    // 1024^2 1.28, 1.28; 1100^2 1.32, 1.17; 1200^2 1.08, 1.01 (whole runs of 100 steps
-    // 0.88); 1300^2 1.00, 0.93; 1400^2 0.94, 0.90; other columns: 511^2 1.40, 1.39; 700x702
-    // 1.49, 1.44; 777x1001 1.15, 1.05 (10 steps 0.87); 1023x1025 0.86, 0.83; 1500x1002
-    // 0.74, 0.68.  Four steps: 512^2 1.22, 640x900 1.09, 900^2 0.77.
-    const long long n = (long long)R * C;
-    if (!fills_tiles(R, C) || n > (C % 4 == 0 ? 1250000 : 550000)) return 0;
-    if (S < (n <= 500000 ? 4 : 8)) return 0;
-    return even_depth(table(R, C, true), S);
+    // The reverse tiles pay in one round: a workgroup of more than two rows a lane fills
+    // a compute unit, of two rows half of one. Speed-up over the streamed pairs: one
+    // round, all gradients of 40 sizes, 1.02 to 1.5 (1024^2 50 steps, 200 tiles, 1.28;
+    // 1164^2 60, 253, 1.13; 512^2, two rows, 430, 1.39), 2200x700 60 steps 0.97; beyond,
+    // 2 columns 4 rows 0.63 to 0.91 (600x1000 16 steps, 399 tiles, 0.86; 1200^2 8, 950,
+    // 0.66), 4 columns 0.87 to 1.01 (1400^2 24 steps, 490, 1.01). In a chain of recorded
+    // segments the reverse passes share the chip with the recording of the next one, and
+    // two rounds are the faster single pass (8 steps, 1400^2, 390 tiles, 1.09, 2048x1000
+    // 1.11; alone 0.88, 0.91). Where columns are no multiple of 4 a lane may hold a fold
+    // or a wrap and reads column by column, for which 4 columns of 4 rows have too few
+    // registers (1023x1025 8 and 50 steps 0.86, 0.83, 1500x1002 0.74, 0.68). Passes of
+    // two steps are bound by memory (333x1001 0.86, 1300^2 0.90); of four 512^2 1.22,
+    // 1100^2 1.01.
+    if (!fills_tiles(R, C) || S < 4) return 0;
+    const int d = even_depth(table(R, C, true), S);
+    const TileShape sh = tile_adjoint_shape(R, C, d);
+    if (d < 4 || (C % 4 != 0 && sh.cpl == 4 && sh.rw == 4)) return 0;
+    const bool two_rounds = sh.cpl == 2 ? sh.rw == 2 : chain && S == 8 && d == 8 && C % 4 == 0;
+    return tiles_of(R, C, sh) <= (two_rounds ? 512 : 256) ? d : 0;
 }
 
 TileShape tile_adjoint_shape(int R, int C, int K) { return table(R, C, true).shape(K); }

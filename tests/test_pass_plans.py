@@ -92,25 +92,41 @@ def test_runs_the_resident_tiles_are_faster_at(R, C, T, model, bc):
 
 
 record_depth = _lib.lib._ZN2rd17tile_record_depthEiix
-adjoint_depth = _lib.lib._ZN2rd18tile_adjoint_depthEiix
-for _f in (record_depth, adjoint_depth):
-    _f.argtypes, _f.restype = [ctypes.c_int, ctypes.c_int, ctypes.c_longlong], ctypes.c_int
+_adjoint_depth = _lib.lib._ZN2rd18tile_adjoint_depthEiixb
+record_depth.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_longlong]
+_adjoint_depth.argtypes = record_depth.argtypes + [ctypes.c_bool]
+record_depth.restype = _adjoint_depth.restype = ctypes.c_int
+
+
+def adjoint_depth(R, C, S, chain=False):
+    return _adjoint_depth(R, C, S, chain)
 
 
 @pytest.mark.parametrize("R,C,S", [
     (1200, 1200, 100), (1164, 1164, 8), (1300, 1300, 16), (1480, 1480, 400), (1333, 1401, 60),
     (1023, 1025, 8), (1201, 1003, 150), (777, 1001, 10), (1500, 1002, 50), (1024, 1024, 4),
-    (900, 900, 2), (500000, 1, 8), (3, 100000, 50), (900, 1500, 20)])
+    (900, 900, 2), (500000, 1, 8), (3, 100000, 50), (600, 1000, 16), (1400, 1400, 8),
+    (900, 1500, 8), (20000, 20, 100)])
 def test_reverse_passes_the_streamed_pairs_are_faster_at(R, C, S):
     assert adjoint_depth(R, C, S) == 0
 
 
 @pytest.mark.parametrize("R,C,S", [(1, 1, 8), (256, 256, 100), (511, 511, 8), (700, 702, 50),
                                    (1024, 1024, 8), (1024, 1024, 48), (1100, 1100, 400),
-                                   (512, 512, 4)])
+                                   (512, 512, 4), (600, 1000, 24), (900, 1500, 20),
+                                   (1164, 1164, 60), (1024, 1280, 16), (701, 803, 16),
+                                   (1100, 1100, 4)])
 def test_reverse_passes_the_resident_tiles_are_faster_at(R, C, S):
     d = adjoint_depth(R, C, S)
     assert d >= 2 and d % 2 == 0
+
+
+def test_reverse_passes_of_chained_segments():
+    """Beside the next segment's recording two rounds of tiles are the faster pass."""
+    for R, C in ((1400, 1400), (1300, 1300), (2048, 1000)):
+        assert adjoint_depth(R, C, 8) == 0 and adjoint_depth(R, C, 8, True) == 8, (R, C)
+    for R, C, S in ((1400, 1400, 16), (1333, 1401, 8), (1200, 1200, 8), (2000, 2000, 8)):
+        assert adjoint_depth(R, C, S, True) == 0, (R, C)
 
 
 def test_recordings_on_resident_tiles():
