@@ -236,8 +236,14 @@ int tile_record_depth(int R, int C, long long n)
 {
     // Speed-up of a run over the streamed recording: 8 steps 1.2 to 1.7 on 20 sizes of
     // 256^2 to 2400^2, 50 steps 1.3 to 2.1; 6 steps 1.0 to 1.35; 2 steps 0.8 to 1.0.
-    if ((long long)R * C > 6000000 || !fills_tiles(R, C) || n < 6) return 0;
-    return even_depth(table(R, C, false), n);
+    // Four steps 0.99 to 1.19 on 40 sizes, but 0.93 to 1.05 where a compute unit, which
+    // holds 16 wavefronts, has one tile of 8 or 10 with 5 or 6 rows a lane to wait for
+    // (900x1500 0.93, 1164^2 0.94, 1201x1003 0.96; five steps of 2301x2303 0.96).
+    if ((long long)R * C > (n < 6 ? 5000000 : 6000000) || !fills_tiles(R, C) || n < 4) return 0;
+    const int d = even_depth(table(R, C, false), n);
+    const TileShape sh = tile_shape(R, C, d);
+    if (n < 6 && (d < 4 || (sh.cpl == 2 && sh.rw >= 5 && sh.w >= 8 && sh.w <= 10))) return 0;
+    return d;
 }
 
 TileShape tile_shape(int R, int C, int K) { return table(R, C, false).shape(K); }

@@ -130,8 +130,10 @@ def test_reverse_passes_of_chained_segments():
 
 
 def test_recordings_on_resident_tiles():
-    for R, C, n in ((1024, 1024, 2), (2200, 2200, 4), (2, 1000000, 50), (500000, 4, 8),
-                    (2500, 2500, 50)):
+    for R, C, n in ((1024, 1024, 2), (900, 1500, 4), (1164, 1164, 4), (2301, 2303, 5),
+                    (2, 1000000, 50), (500000, 4, 8), (2500, 2500, 50)):
         assert record_depth(R, C, n) == 0, (R, C, n)
     for R, C, n in ((256, 256, 100), (1024, 1024, 8), (1333, 1401, 20), (2301, 2303, 50)):
         assert record_depth(R, C, n) >= 6, (R, C, n)
+    for R, C in ((512, 512), (900, 900), (2048, 1000), (2200, 2200)):
+        assert record_depth(R, C, 4) == 4, (R, C)
