@@ -185,25 +185,47 @@ bool fills_tiles(int R, int C)
     return m >= 64 || (m >= 16 && n <= 1 << 19) || n <= 1 << 16;
 }
 
-// Whether a T-step run of plain passes is faster on resident tiles, whose plan
-// would have passes of K steps.  From 9000 timed passes on 60 sizes; speed-up over
-// the streamed passes in brackets.
+// Streamed passes that T steps take: of up to 8 each, the other models' of 1, 2, 4 or 8.
+long long streamed_passes(int model, long long T)
+{
+    return T / 8 + (model == MODEL_FHN ? T % 8 != 0 : __builtin_popcount((unsigned)(T % 8)));
+}
+
+// Whether a T-step run of plain passes is faster on resident tiles by this plan.
+// From 9000 timed passes on 60 sizes; speed-up over the streamed passes in brackets.
 // Few steps are bound by memory, which a tile does not touch while it computes:
-// 777x1301 3 steps (0.94), 2000x600 5 (0.95 on a torus), 1792^2 2 (0.79); six steps
-// gain from 1.0 (2048^2) to 1.2.  The other models' streamed passes have 1, 2, 4 or 8
-// steps, so 3 and 5 take them two (3 steps, Gray-Scott: 256^2 1.9, 1536^2 1.5).
-// From 4.3M cells on the streamed passes fill the chip and only deep tiles gain:
-// 2400^2, where pairs of wavefronts are the other choice, 11 steps a pass (0.97), 12
-// (1.04), 16 (1.07); without pairs 2300x2301 8 (0.86), 9 (1.27), 11 (1.05), 16 (1.07).
-// The CNN's streamed pass has two columns per lane at most: 2300x2298 8 (1.00),
-// 2448^2 8 (1.21), 3000^2 8 (1.16); 4096^2 8 (0.98), 12 (1.16), 14 (1.06), 16 (1.03).
-bool tiles_pay(int R, int C, int bc, int model, int K)
+// 777x1301 3 steps (0.94), 1792^2 2 (0.79), 2048^2 4 (0.90).  Five gain 1.0 to 1.2 up to 4M
+// cells, unless a compute unit has one tile of 10 wavefronts with 5 or 6 rows a lane to
+// wait for (2000x600 0.94); six gain from 1.0 (2048^2) to 1.2.  The other models take two
+// streamed passes for 3 and 5 (3 steps, Gray-Scott: 256^2 1.9, 1536^2 1.5), and four of the
+// CNN gain 0.97 to 1.13.
+// From 4.3M cells on the streamed passes fill the chip, and one pass of tiles pays for
+// two of up to 10 steps (12 on a zero-flux grid) and for three: 2304^2 9 steps 1.13, 1.29
+// zero-flux; 2448^2 10 1.03, 1.10, 12 1.07 zero-flux; 2400^2 11 0.93, but Gray-Scott,
+// three, 1.28; the CNN 2600x2665 5 1.28, 4096^2 3 1.27, 5 1.36, 7 1.19.  Other runs gain in
+// deep tiles only: 2300x2301 8 steps a pass (0.86), 9 (1.27), 16 (1.07); where pairs of
+// wavefronts are the other choice 2304^2 10 (1.07 zero-flux, 0.94), 2400^2 12 (0.90, 0.82),
+// 16 (1.00, 0.91), 2448^2 14 (1.06, 0.98), and a compute unit's one tile of 10 wavefronts,
+// three on two of its four SIMDs, 2200^2 10 (0.95).  The CNN's streamed pass has two
+// columns per lane at most: 2300x2298 8 (1.00), 2448^2 8 (1.21), 3000^2 8 (1.16); 4096^2 8
+// (0.98), 9 (1.16), 12 (1.16), 16 (1.03).
+bool tiles_pay(int R, int C, int bc, int model, long long T, const TilePlan &plan)
 {
     const long long n = (long long)R * C;
-    if (n <= kMidTileCells) return true;
-    if (model == MODEL_CNN) return n <= 12000000 ? K >= 8 : n <= 20000000 && K >= 10 && K <= 13;
-    if (!pair_pass(bc, R, C, kPairCpl, kPairDepth)) return n <= 6000000 && K >= 9;
-    return K >= 12 && n <= (bc == BC_PERIODIC ? 4500000 : 6000000);
+    const TileShape &sh = plan.base;
+    if (n <= kMidTileCells) {
+        if (model != MODEL_FHN || T >= 6) return true;
+        return n <= 4000000 && !(sh.cpl == 2 && sh.rw >= 5 && sh.w == 10);
+    }
+    const long long others = streamed_passes(model, T);
+    const long long most = model == MODEL_FHN ? 6000000 : model == MODEL_CNN ? 20000000 : 7000000;
+    if (plan.passes == 1 && n <= most &&
+        (others > 2 || (others == 2 && T <= (bc == BC_ZEROFLUX ? 12 : 10))))
+        return true;
+    if (model == MODEL_CNN) return sh.K >= (n <= 12000000 ? 8 : 9);
+    if (!pair_pass(bc, R, C, kPairCpl, kPairDepth)) return n <= 6000000 && sh.K >= 9;
+    if (bc == BC_PERIODIC) return n <= 4500000 && sh.K >= 12;
+    return n <= 5500000 ? sh.K >= (sh.w == 10 ? 12 : 9) : n <= 6000000 && sh.K >= 13;
 }
 
 }  // namespace
@@ -211,7 +233,7 @@ bool tiles_pay(int R, int C, int bc, int model, int K)
 bool tile_plan(int R, int C, int bc, int model, long long T, TilePlan *plan)
 {
     if ((long long)R * C > 20000000 || !fills_tiles(R, C)) return false;
-    if (T < 6 && (model == MODEL_FHN || (T != 3 && T != 5))) return false;
+    if (T < (model == MODEL_FHN ? 5 : 3) || (T == 4 && model != MODEL_CNN)) return false;
     Table &tb = table(R, C, false);
     double best = INFINITY;
     for (int K = kMaxTileDepth; K >= 1; --K) {
@@ -229,7 +251,7 @@ bool tile_plan(int R, int C, int bc, int model, long long T, TilePlan *plan)
             plan->deep = tb.shape((int)(more ? lo + 1 : lo));
         }
     }
-    return best < INFINITY && tiles_pay(R, C, bc, model, plan->base.K);
+    return best < INFINITY && tiles_pay(R, C, bc, model, T, *plan);
 }
 
 int tile_record_depth(int R, int C, long long n)

@@ -72,8 +72,9 @@ def _plan(R, C, T, model=FHN, bc=1):
     (4, 500000, 8, FHN), (2, 1000000, 50, FHN), (3000000, 1, 100, FHN), (100000, 40, 7, FHN),
     (100000, 3, 8, GRAY_SCOTT), (1, 3000000, 16, CNN),
     # grids on which the streamed passes fill the chip
-    (2300, 2301, 8, FHN), (2400, 2400, 8, FHN), (2400, 2400, 11, FHN), (2300, 2298, 8, GRAY_SCOTT),
-    (3100, 3333, 4, CNN), (4096, 4096, 8, CNN), (2500, 2500, 1000, FHN), (6000, 6000, 12, CNN)])
+    (2300, 2301, 8, FHN), (2400, 2400, 8, FHN), (2400, 2400, 20, FHN), (2300, 2298, 8, GRAY_SCOTT),
+    (3100, 3333, 4, CNN), (4096, 4096, 8, CNN), (2500, 2500, 1000, FHN), (6000, 6000, 12, CNN),
+    (2048, 2048, 5, FHN), (3100, 3333, 3, GRAY_SCOTT), (2400, 2400, 24, FHN), (6000, 6000, 3, CNN)])
 def test_runs_the_streamed_passes_are_faster_at(R, C, T, model, bc):
     assert _plan(R, C, T, model, bc) is None
 
@@ -83,7 +84,11 @@ def test_runs_the_streamed_passes_are_faster_at(R, C, T, model, bc):
     (1, 1, 10, FHN), (128, 128, 10, FHN), (256, 256, 1000, FHN), (777, 1301, 300, FHN),
     (1024, 1024, 6, FHN), (10000, 33, 8, FHN), (2048, 2048, 1000, FHN), (2300, 2301, 9, FHN),
     (2048, 2048, 200, GRAY_SCOTT), (256, 256, 3, GRAY_SCOTT), (512, 512, 5, CNN),
-    (2603, 2900, 39, CNN), (4096, 4096, 12, CNN)])
+    (2603, 2900, 39, CNN), (4096, 4096, 12, CNN),
+    (1024, 1024, 5, FHN), (1000, 4000, 5, FHN), (2304, 2304, 9, FHN), (2400, 2400, 10, FHN),
+    (2304, 2304, 3, GRAY_SCOTT), (2600, 2665, 7, GRAY_SCOTT), (2400, 2400, 11, GRAY_SCOTT),
+    (1535, 1535, 4, CNN), (4096, 4096, 3, CNN), (4096, 4096, 9, CNN),
+    (4096, 4096, 5, CNN), (3500, 3500, 7, CNN)])
 def test_runs_the_resident_tiles_are_faster_at(R, C, T, model, bc):
     p = _plan(R, C, T, model, bc)
     assert p is not None
