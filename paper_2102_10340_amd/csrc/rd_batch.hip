@@ -854,9 +854,12 @@ int batch_record(rdcnn_batch *b, long long T, float *traj, bool even, const char
     // plain pass's led sweeps on 64 x 1024^2 (full: 64 rows; even-time: 32 rows,
     // 0.57 Tcell-steps/s against 0.50 at 64); smaller batches take less where
     // that fills the chip (6 of 500 x 640, even-time: 31 us a pass against 40).
-    // Full recording, whose stores lead, stays at 64 rows from 1152 such tiles on
-    // (8 steps, us, 64 rows / the cheapest cut: two of 2048^2 243 / 262, 3000^2
-    // 256 / 271; four of 1024^2, 640 tiles, 155 / 106).
+    // Full recording, whose stores lead, takes 2 columns and 64 rows where that is just
+    // over a wavefront a SIMD (8 steps, us, so / the cheapest cut: two of 2048^2, 1216
+    // tiles, 241 / 262; 16 of 700x702, 1232, 262 / 292; 3000^2, 1269, 256 / 271), the cheapest
+    // cut below (four of 1024^2, 640, 155 / 106; 64 of 70x1000, 1152, 150 / 107) and the
+    // cheaper columns of 64 rows above (1024 of 128^2, 4096, 683 / 487; five of 20000x1,
+    // 1565, 99 / 64; 1000 of 100^2, 2000, 337 / 335).
     if (!b->depth) {
         int *cut = b->rec_cut[even ? 1 : 0];
         if (!cut[0]) {
@@ -865,8 +868,10 @@ int batch_record(rdcnn_batch *b, long long T, float *traj, bool even, const char
             cut[1] = 64;
             if (even)
                 best_cut(sizes, kStepCost, 1, 2, {8, 16, 32}, &cut[0], &cut[1]);
-            else if (tiles_in(sizes, 2, 8, 64) < 1152)
+            else if (const long long n = tiles_in(sizes, 2, 8, 64); n < 1160)
                 best_cut(sizes, kStepCost, 1, 2, {8, 16, 32, 64}, &cut[0], &cut[1]);
+            else if (n > 1300)
+                best_cut(sizes, kStepCost, 1, 2, {64}, &cut[0], &cut[1]);
         }
         cpl = cut[0];
         seg = cut[1];
