@@ -228,35 +228,38 @@ int side_stream(hipStream_t *out, const char *who)
 }  // namespace
 
 // Whether a kernel may read the n-cell planes at src and src + n into u and v in place
-// of two copies: all in plain memory of one device, aligned, inside their allocations
+// of two copies: to plain memory of the state's device, aligned, inside its allocations
 // (a copy past one is refused, a kernel would write there) and apart (a second copy
-// reads what the first has written).
+// reads what the first has written).  The state is the handle's own, which its kernels
+// write; planes of one allocation are looked up once (0.2 us of host time a lookup).
 bool rd::kernel_may_read(const float *src, long long n, const float *u, const float *v)
 {
     const size_t plane = sizeof(float) * (size_t)n;
-    const struct {
-        const float *p;
-        size_t bytes;
-    } at[3] = {{src, 2 * plane}, {u, plane}, {v, plane}};
-    int device = -1;
-    for (int i = 0; i < 3; ++i) {
-        const char *p = (const char *)at[i].p;
-        for (int j = 0; j < i; ++j) {
-            const char *q = (const char *)at[j].p;
-            if (p < q + at[j].bytes && q < p + at[i].bytes) return false;
+    const char *const from = (const char *)src, *const at[2] = {(const char *)u, (const char *)v};
+    if ((uintptr_t)u % sizeof(float) != 0 || (uintptr_t)v % sizeof(float) != 0) return false;
+    if (at[0] < at[1] + plane && at[1] < at[0] + plane) return false;
+    for (const char *p : at)
+        if (p < from + 2 * plane && from < p + plane) return false;
+    hipPointerAttribute_t a;
+    if (hipPointerGetAttributes(&a, src) != hipSuccess) {
+        (void)hipGetLastError();  // an unregistered pointer is no error here
+        return false;
+    }
+    const int device = a.device;
+    const char *base = nullptr;
+    size_t size = 0;
+    for (const char *p : at) {
+        if (!base || p < base || p >= base + size) {
+            hipDeviceptr_t start = nullptr;
+            if (hipPointerGetAttributes(&a, p) != hipSuccess ||
+                hipMemGetAddressRange(&start, &size, (hipDeviceptr_t)p) != hipSuccess) {
+                (void)hipGetLastError();
+                return false;
+            }
+            if (a.type != hipMemoryTypeDevice || a.isManaged || a.device != device) return false;
+            base = (const char *)start;
         }
-        hipPointerAttribute_t a;
-        hipDeviceptr_t base = nullptr;
-        size_t size = 0;
-        if ((uintptr_t)p % sizeof(float) != 0) return false;
-        if (hipPointerGetAttributes(&a, p) != hipSuccess ||
-            hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
-            (void)hipGetLastError();  // an unregistered pointer is no error here
-            return false;
-        }
-        if (a.type != hipMemoryTypeDevice || a.isManaged || (i > 0 && a.device != device)) return false;
-        if (p < (const char *)base || p + at[i].bytes > (const char *)base + size) return false;
-        device = a.device;
+        if (p < base || plane > size - (size_t)(p - base)) return false;
     }
     return true;
 }
