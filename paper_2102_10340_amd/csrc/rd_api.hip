@@ -1275,8 +1275,9 @@ int rdcnn_step_bwd_ckpt(rdcnn_t h, const float *ckpt_dev, long long T, long long
     // One partial buffer for every segment: cleared once, folded once.
     const long long Llast = T - (nseg - 1) * S;
     PairPlan pl, plast;
-    int rc = plan_pairs(h, Smax, 2, who, &pl, true);
-    if (rc == RDCNN_OK) rc = plan_pairs(h, Llast, 2, who, &plast, true);
+    const bool chain = nseg > 1;
+    int rc = plan_pairs(h, Smax, 2, who, &pl, chain);
+    if (rc == RDCNN_OK) rc = plan_pairs(h, Llast, 2, who, &plast, chain);
     if (rc != RDCNN_OK) return rc;
     const long long need = pl.need > plast.need ? pl.need : plast.need;
     if ((rc = ensure_partial(h, need, who)) != RDCNN_OK) return rc;
@@ -1322,7 +1323,7 @@ int rdcnn_step_bwd_ckpt(rdcnn_t h, const float *ckpt_dev, long long T, long long
         // Reverse passes of segment k on the handle's stream, overlapping the
         // recompute of segment k-1.
         PairPlan plk;
-        if ((rc = plan_pairs(h, L, 2, who, &plk, true)) != RDCNN_OK) return rc;
+        if ((rc = plan_pairs(h, L, 2, who, &plk, chain)) != RDCNN_OK) return rc;
         rc = run_pairs(h, traj, 2, L, pp, plk, h->partial, dtheta_accum, who, false);
         if (rc != RDCNN_OK) return rc;
         if ((e = hipEventRecord(done[b], h->stream)) != hipSuccess) return hip_fail(e, who);
